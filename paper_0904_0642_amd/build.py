@@ -11,7 +11,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsu3hb.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["update.hip", "aux.hip", "capi.cpp"]
+DIMS = range(2, 7)
+# (source, object, flags): the update kernels are compiled once per dimension
+UNITS = [(f"{src}.hip", f"{src}{d}", [f"-DSU3HB_DIM={d}"]) for src in ("update",) for d in DIMS]
+UNITS += [(f"{src}.hip", src, []) for src in ("update", "aux")] + [("capi.cpp", "capi", [])]
 ARCH = os.environ.get("SU3HB_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [
@@ -23,19 +26,20 @@ FLAGS = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = ["hipcc", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS
+def _compile(unit) -> str:
+    src, name, flags = unit
+    obj = os.path.join(BUILD, name + ".o")
+    cmd = ["hipcc", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS + flags
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
+        raise RuntimeError(f"hipcc failed for {src} {flags}:\n{r.stderr}")
     return obj
 
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        objs = list(ex.map(_compile, UNITS))
     tmp = OUT + ".tmp"
     cmd = ["hipcc", f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

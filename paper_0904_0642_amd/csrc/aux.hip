@@ -112,11 +112,12 @@ __global__ void __launch_bounds__(256) plaquette_kernel(PlaqArgs a)
 // over the planes (nu, mu), nu < mu, written by the parity-1 update slices,
 // in nc classes: nc = 1 for one layer; nc = 3 for two layers (0: base site in
 // layer 0 and all links in layer 0, 1: base in layer 0 otherwise, 2: base in
-// layer 1).  One block adds them up in a fixed order.
+// layer 1).  One block per sweep adds them up in a fixed order.
 __global__ void __launch_bounds__(1024) measure_finalize_kernel(const double *meas, int D, uint32_t nblocks, int nc,
                                                                  double V, int nlat, double beta0, double beta1,
-                                                                 double *out, double *series, uint32_t *cursor)
+                                                                 double *series)
 {
+    meas += size_t(blockIdx.x) * D * nblocks * nc;
     double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // [spacelike, timelike] x class
     const uint32_t bd = blockDim.x;
     for (int mu = 1; mu < D; ++mu) {
@@ -161,28 +162,22 @@ __global__ void __launch_bounds__(1024) measure_finalize_kernel(const double *me
         o[3] = (t0 + t1) / nlayer;
         o[4] = nlat == 2 ? t2 / nlayer : nan;
         o[5] = beta0 * t0 + beta1 * (t1 + t2);
-        for (int i = 0; i < 6; ++i) out[i] = o[i];
-        if (series) {
-            const uint32_t k = atomicAdd(cursor, 1u);
-            for (int i = 0; i < 6; ++i) series[size_t(k) * 6 + i] = o[i];
-        }
+        for (int i = 0; i < 6; ++i) series[size_t(blockIdx.x) * 6 + i] = o[i];
     }
 }
 
-hipError_t launch_measure_finalize(hipStream_t st, const double *meas, int D, uint32_t nblocks, int nc, double V,
-                                   int nlat, double beta0, double beta1, double *out, double *series,
-                                   uint32_t *cursor)
+hipError_t launch_measure_finalize(hipStream_t st, const double *meas, int n, int D, uint32_t nblocks, int nc,
+                                   double V, int nlat, double beta0, double beta1, double *series)
 {
     if (nc != 1 && nc != 3) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(measure_finalize_kernel, dim3(1), dim3(1024), 0, st, meas, D, nblocks, nc, V, nlat, beta0,
-                       beta1, out, series, cursor);
+    hipLaunchKernelGGL(measure_finalize_kernel, dim3(n), dim3(1024), 0, st, meas, D, nblocks, nc, V, nlat, beta0,
+                       beta1, series);
     return hipGetLastError();
 }
 
 // One block per replica: fixed-order sum of its block partials, normalised.
 __global__ void __launch_bounds__(256) plaquette_finalize_kernel(const RepDesc *reps, int D,
-                                                                  const double *partials, double *out,
-                                                                  double *series, uint32_t *cursor)
+                                                                  const double *partials, double *out)
 {
     const RepDesc &rep = reps[blockIdx.x];
     double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -204,10 +199,6 @@ __global__ void __launch_bounds__(256) plaquette_finalize_kernel(const RepDesc *
         o[4] = rep.nlat == 2 ? v[3] / nlayer : nan;
         o[5] = v[4];
         for (int i = 0; i < 6; ++i) out[size_t(blockIdx.x) * 6 + i] = o[i];
-        if (series) {
-            const uint32_t k = atomicAdd(cursor, 1u);
-            for (int i = 0; i < 6; ++i) series[size_t(k) * 6 + i] = o[i];
-        }
     }
 }
 
@@ -241,11 +232,9 @@ hipError_t launch_plaquette(int D, int prec, dim3 g, dim3 b, hipStream_t st, con
 }
 
 hipError_t launch_plaquette_finalize(hipStream_t st, const RepDesc *reps, int nrep, int D,
-                                     const double *partials, double *out, double *series,
-                                     uint32_t *series_cursor)
+                                     const double *partials, double *out)
 {
-    hipLaunchKernelGGL(plaquette_finalize_kernel, dim3(nrep), dim3(256), 0, st, reps, D, partials, out,
-                       series, series_cursor);
+    hipLaunchKernelGGL(plaquette_finalize_kernel, dim3(nrep), dim3(256), 0, st, reps, D, partials, out);
     return hipGetLastError();
 }
 
@@ -524,6 +513,11 @@ __global__ void counter_set_kernel(uint32_t *ctr, uint32_t value)
     if (threadIdx.x == 0) atomicExch(ctr, value);
 }
 
+__global__ void measure_begin_kernel(uint32_t *sweep)
+{
+    if (threadIdx.x == 0) sweep[2] = sweep[0];
+}
+
 __global__ void u32_zero_kernel(uint32_t *p, int n)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -570,6 +564,12 @@ hipError_t launch_counter_add(hipStream_t st, uint32_t *ctr, uint32_t add)
 hipError_t launch_counter_set(hipStream_t st, uint32_t *ctr, uint32_t value)
 {
     hipLaunchKernelGGL(counter_set_kernel, dim3(1), dim3(64), 0, st, ctr, value);
+    return hipGetLastError();
+}
+
+hipError_t launch_measure_begin(hipStream_t st, uint32_t *sweep)
+{
+    hipLaunchKernelGGL(measure_begin_kernel, dim3(1), dim3(64), 0, st, sweep);
     return hipGetLastError();
 }
 

@@ -46,14 +46,15 @@ int fail(int code, const char *fmt, ...)
 constexpr int kPlaqBlock = 256;
 constexpr uint32_t kSeriesCap = 4096;
 constexpr size_t kStageBytes = size_t(256) << 20;
+constexpr size_t kMeasBytes = size_t(64) << 20;  // partial sums kept before they are added up
 
-// A captured sweep, keyed by its couplings, kind (n_hit; 0 = overrelaxation)
-// and measurement.  A few are kept so that heatbath and overrelaxation sweeps
+// A captured sweep, keyed by its couplings, kind (n_hit; 0 = overrelaxation),
+// measurement and whether it keeps counters.  A few are kept so that heatbath and overrelaxation sweeps
 // can alternate without capturing again.
 struct GraphCache {
     bool valid = false;
     double b0 = 0, b1 = 0;
-    int nhit = 0, measure = 0;
+    int nhit = 0, measure = 0, counters = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     uint64_t used = 0;
@@ -79,11 +80,10 @@ struct su3hb_lattice {
     StatSlot *d_stats = nullptr;
     StatSlot *d_stats_out = nullptr;
     double *d_partials = nullptr;
-    double *d_meas = nullptr;     // fused measurement partials, [D][update blocks]
+    double *d_meas = nullptr;     // fused measurement partials, [sweep][D][update blocks][classes]
     size_t meas_cap = 0;
     double *d_plaq = nullptr;
     double *d_series = nullptr;
-    uint32_t *d_cursor = nullptr;
     unsigned long long *d_maxdef = nullptr;
     double *d_stage = nullptr;
     uint32_t *d_bar = nullptr;    // grid-barrier counters of persistent launches
@@ -202,12 +202,11 @@ int alloc_common(su3hb_lattice *L)
     L->num_cus = prop.multiProcessorCount;
     HIPCHK(hipStreamCreateWithFlags(&L->cap, hipStreamNonBlocking));
     HIPCHK(hipMalloc(&L->d_reps, sizeof(RepDesc) * L->reps.size()));
-    HIPCHK(hipMalloc(&L->d_sweep, sizeof(uint32_t)));
+    HIPCHK(hipMalloc(&L->d_sweep, sizeof(uint32_t) * kSweepWords));
     HIPCHK(hipMalloc(&L->d_stats, sizeof(StatSlot) * kStatSlots));
     HIPCHK(hipMalloc(&L->d_stats_out, sizeof(StatSlot)));
     HIPCHK(hipMalloc(&L->d_plaq, sizeof(double) * 6 * L->reps.size()));
     HIPCHK(hipMalloc(&L->d_series, sizeof(double) * 6 * kSeriesCap));
-    HIPCHK(hipMalloc(&L->d_cursor, sizeof(uint32_t)));
     HIPCHK(hipMalloc(&L->d_maxdef, sizeof(unsigned long long)));
     HIPCHK(hipMalloc(&L->d_bar, sizeof(uint32_t) * kBarrierWords));
     layout_reps(L);
@@ -215,7 +214,6 @@ int alloc_common(su3hb_lattice *L)
     int rc = upload_reps(L);
     if (rc) return rc;
     HIPCHK(launch_counter_set(L->stream, L->d_sweep, 0));
-    HIPCHK(launch_counter_set(L->stream, L->d_cursor, 0));
     HIPCHK(launch_stats_zero(L->stream, L->d_stats));
     return SU3HB_OK;
 }
@@ -259,7 +257,6 @@ void destroy(su3hb_lattice *L)
     hipFree(L->d_meas);
     hipFree(L->d_plaq);
     hipFree(L->d_series);
-    hipFree(L->d_cursor);
     hipFree(L->d_maxdef);
     hipFree(L->d_stage);
     hipFree(L->d_bar);
@@ -352,7 +349,7 @@ int effective_order(const su3hb_lattice *L)
     return base_order(L) | (L->order & kOrderReverse) | (stage_applies(L) ? kOrderStage : 0);
 }
 
-UpdateArgs update_args(const su3hb_lattice *L, double b0, double b1, int nhit)
+UpdateArgs update_args(const su3hb_lattice *L, double b0, double b1, int nhit, bool counters)
 {
     UpdateArgs a;
     std::memset(&a, 0, sizeof a);
@@ -390,7 +387,7 @@ UpdateArgs update_args(const su3hb_lattice *L, double b0, double b1, int nhit)
     a.beta1 = b1;
     a.meas_classes = 1;
     a.sweep = L->d_sweep;
-    a.stats = L->d_stats;
+    a.stats = counters ? L->d_stats : nullptr;
     a.total_blocks = L->upd_blocks;
     return a;
 }
@@ -402,7 +399,7 @@ dim3 update_grid(const su3hb_lattice *L)
     return dim3(g);
 }
 
-int enqueue_plaquette(su3hb_lattice *L, hipStream_t st, double b0, double b1, double *series)
+int enqueue_plaquette(su3hb_lattice *L, hipStream_t st, double b0, double b1)
 {
     PlaqArgs pa;
     std::memset(&pa, 0, sizeof pa);
@@ -415,14 +412,10 @@ int enqueue_plaquette(su3hb_lattice *L, hipStream_t st, double b0, double b1, do
     pa.partials = L->d_partials;
     pa.total_blocks = L->plq_blocks;
     HIPCHK(launch_plaquette(L->nd, L->prec, dim3(L->plq_blocks), dim3(kPlaqBlock), st, pa));
-    HIPCHK(launch_plaquette_finalize(st, L->d_reps, L->nrep, L->nd, L->d_partials, L->d_plaq, series,
-                                     L->d_cursor));
+    HIPCHK(launch_plaquette_finalize(st, L->d_reps, L->nrep, L->nd, L->d_partials, L->d_plaq));
     return SU3HB_OK;
 }
 
-// The plaquettes of a single-layer lattice are measured inside the parity-1
-// update slices (see update.hip); two layers and batches use the plaquette
-// kernel after the sweep.
 // Single lattices (one or two layers) measure inside the parity-1 update
 // slices; batches use the plaquette kernel.
 bool fused_measure(const su3hb_lattice *L) { return !L->batch; }
@@ -430,10 +423,22 @@ bool fused_measure(const su3hb_lattice *L) { return !L->batch; }
 // Measurement classes: one layer 1; two layers 3 (by base layer and tags).
 int meas_classes(const su3hb_lattice *L) { return L->reps[0].nlat == 2 ? 3 : 1; }
 
-int ensure_meas(su3hb_lattice *L)
+// Doubles of partial sums that one measured sweep writes.
+size_t meas_doubles(const su3hb_lattice *L)
 {
-    const size_t need = size_t(L->nd) * L->upd_blocks * size_t(meas_classes(L));
-    if (need <= L->meas_cap) return SU3HB_OK;
+    return size_t(L->nd) * L->upd_blocks * size_t(meas_classes(L));
+}
+
+// Room for the partial sums of n sweeps, or of as many as kMeasBytes hold
+// (one at least); *slots says how many.
+int ensure_meas(su3hb_lattice *L, int n, int *slots)
+{
+    const size_t one = meas_doubles(L), most = std::max<size_t>(1, kMeasBytes / sizeof(double) / one);
+    *slots = int(std::min<size_t>(size_t(n), most));
+    if (one * size_t(*slots) <= L->meas_cap) return SU3HB_OK;
+    // at least 16 sweeps and twice the last size: calls of growing length do
+    // not allocate each time
+    const size_t need = one * std::min(most, std::max({size_t(*slots), size_t(16), 2 * L->meas_cap / one}));
     // captured sweeps hold the old buffer's address
     HIPCHK(hipStreamSynchronize(L->stream));
     drop_graph(L);
@@ -446,15 +451,15 @@ int ensure_meas(su3hb_lattice *L)
     return SU3HB_OK;
 }
 
-// One sweep: parity 0 then 1, directions 0..D-1 inside, then the counter and
-// (measure != 0) the plaquettes into the series.  `timed` (optional) records
-// an event pair around every update launch and the plaquette launch.
-int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nhit, int measure,
+// One sweep: parity 0 then 1, directions 0..D-1 inside; the last slice steps
+// the counter.  measure != 0 (single lattices): the parity-1 slices leave the
+// partial sums of the plaquettes (finish_measure adds them up).  `timed`
+// (optional) records an event pair around every update launch.
+int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nhit, int measure, bool counters,
                   std::vector<int> *timed = nullptr, size_t *ev = nullptr)
 {
-    UpdateArgs a = update_args(L, b0, b1, nhit);
-    const bool fused = measure && fused_measure(L);
-    if (fused) {
+    UpdateArgs a = update_args(L, b0, b1, nhit, counters);
+    if (measure) {
         a.meas = L->d_meas;
         a.meas_classes = meas_classes(L);
     }
@@ -482,44 +487,24 @@ int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nh
                 timed->push_back(0);
             }
         }
-    HIPCHK(launch_counter_add(st, L->d_sweep, 1));
-    if (!measure) return SU3HB_OK;
-    if (fused) {
-        if (timed) HIPCHK(hipEventRecord(L->events[(*ev)++], st));
-        HIPCHK(launch_measure_finalize(st, L->d_meas, L->nd, L->upd_blocks, meas_classes(L), double(L->reps[0].V),
-                                       int(L->reps[0].nlat), b0, b1, L->d_plaq, L->d_series, L->d_cursor));
-        if (timed) {
-            HIPCHK(hipEventRecord(L->events[(*ev)++], st));
-            timed->push_back(1);
-        }
-        return SU3HB_OK;
-    }
-    if (timed) HIPCHK(hipEventRecord(L->events[(*ev)++], st));
-    PlaqArgs pa;
-    std::memset(&pa, 0, sizeof pa);
-    pa.links = L->links;
-    pa.reps = L->d_reps;
-    pa.nrep = L->nrep;
-    pa.beta0 = b0;
-    pa.beta1 = b1;
-    pa.use_rep_beta = L->batch ? 1 : 0;
-    pa.partials = L->d_partials;
-    pa.total_blocks = L->plq_blocks;
-    HIPCHK(launch_plaquette(L->nd, L->prec, dim3(L->plq_blocks), dim3(kPlaqBlock), st, pa));
-    if (timed) {
-        HIPCHK(hipEventRecord(L->events[(*ev)++], st));
-        timed->push_back(1);
-    }
-    HIPCHK(launch_plaquette_finalize(st, L->d_reps, L->nrep, L->nd, L->d_partials, L->d_plaq, L->d_series,
-                                     L->d_cursor));
     return SU3HB_OK;
 }
 
-int get_graph(su3hb_lattice *L, double b0, double b1, int nhit, int measure, hipGraphExec_t *out)
+// The plaquettes of the n measured sweeps since launch_measure_begin, into
+// n rows of the series.
+int finish_measure(su3hb_lattice *L, double b0, double b1, int n, double *series)
+{
+    HIPCHK(launch_measure_finalize(L->stream, L->d_meas, n, L->nd, L->upd_blocks, meas_classes(L),
+                                   double(L->reps[0].V), int(L->reps[0].nlat), b0, b1, series));
+    return SU3HB_OK;
+}
+
+int get_graph(su3hb_lattice *L, double b0, double b1, int nhit, int measure, bool counters, hipGraphExec_t *out)
 {
     GraphCache *slot = nullptr;
     for (auto &g : L->graphs)
-        if (g.valid && g.b0 == b0 && g.b1 == b1 && g.nhit == nhit && g.measure == measure) {
+        if (g.valid && g.b0 == b0 && g.b1 == b1 && g.nhit == nhit && g.measure == measure &&
+            g.counters == int(counters)) {
             g.used = ++L->graph_tick;
             *out = g.exec;
             return SU3HB_OK;
@@ -532,7 +517,7 @@ int get_graph(su3hb_lattice *L, double b0, double b1, int nhit, int measure, hip
         }
     drop_slot(*slot);
     HIPCHK(hipStreamBeginCapture(L->cap, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_sweep(L, L->cap, b0, b1, nhit, measure);
+    int rc = enqueue_sweep(L, L->cap, b0, b1, nhit, measure, counters);
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamEndCapture(L->cap, &graph);
     if (rc) {
@@ -551,6 +536,7 @@ int get_graph(su3hb_lattice *L, double b0, double b1, int nhit, int measure, hip
     slot->b1 = b1;
     slot->nhit = nhit;
     slot->measure = measure;
+    slot->counters = counters;
     slot->graph = graph;
     slot->exec = exec;
     slot->used = ++L->graph_tick;
@@ -567,22 +553,18 @@ int check_sweep_room(const su3hb_lattice *L, int n)
     return SU3HB_OK;
 }
 
-int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measure)
+int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measure, bool counters)
 {
     if (n <= 0) return SU3HB_OK;
     if (int rc = check_sweep_room(L, n)) return rc;
-    if (measure && fused_measure(L)) {
-        int rc = ensure_meas(L);
-        if (rc) return rc;
-    }
     if (L->use_graph) {
         hipGraphExec_t exec = nullptr;
-        int rc = get_graph(L, b0, b1, nhit, measure, &exec);
+        int rc = get_graph(L, b0, b1, nhit, measure, counters, &exec);
         if (rc) return rc;
         for (int i = 0; i < n; ++i) HIPCHK(hipGraphLaunch(exec, L->stream));
     } else {
         for (int i = 0; i < n; ++i) {
-            int rc = enqueue_sweep(L, L->stream, b0, b1, nhit, measure);
+            int rc = enqueue_sweep(L, L->stream, b0, b1, nhit, measure, counters);
             if (rc) return rc;
         }
     }
@@ -714,7 +696,7 @@ int apply_launch(su3hb_lattice *L, int block, int order, int waves)
     // a measured parity-1 slice asks for the most LDS: staple snapshots and,
     // when staging, the staging areas
     size_t need = 0, limit = 0;
-    UpdateArgs m = update_args(L, 6.0, 6.0, 8);
+    UpdateArgs m = update_args(L, 6.0, 6.0, 8, true);
     m.parity = 1;
     if (fused_measure(L)) {
         m.meas = reinterpret_cast<double *>(uintptr_t(256));  // only tested for null
@@ -747,12 +729,12 @@ int ensure_events(su3hb_lattice *L, size_t n)
 // Scratch of su3hb_sweep_measure_static: a file-scope device array, so that
 // call allocates nothing.  Each GPU holds its own copy until the process
 // ends; every call on a GPU shares it (calls that overlap on one GPU race).
-// Layout (byte offsets): the replica descriptor, the sweep counter, the
-// series cursor, the last plaquettes, the statistics slots, then the fused
-// measurement's per-block partial sums.
+// Layout (byte offsets): the replica descriptor, the sweep counter, unused
+// bytes, then the fused measurement's per-block partial sums (their place
+// sets the largest lattice that is accepted).
 constexpr size_t kScratchBytes = size_t(8) << 20;
-constexpr size_t kScrRep = 0, kScrSweep = 256, kScrCursor = 512, kScrPlaq = 768, kScrStats = 1024;
-constexpr size_t kScrMeas = kScrStats + sizeof(StatSlot) * kStatSlots;
+constexpr size_t kScrRep = 0, kScrSweep = 256;
+constexpr size_t kScrMeas = size_t(33) << 10;
 constexpr size_t kScratchMeasDoubles = (kScratchBytes - kScrMeas) / sizeof(double);
 static_assert(sizeof(RepDesc) <= kScrSweep - kScrRep, "replica descriptor overflows its scratch slot");
 static_assert(kScrMeas % 256 == 0, "partial sums start on a 256-byte boundary");
@@ -862,7 +844,7 @@ int su3hb_sweep(su3hb_lattice *L, double beta0, double beta1, int n_hit, int n_s
     if (rc) return rc;
     HIPCHK(hipSetDevice(L->device));
     if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
-    rc = run_sweeps(L, beta0, beta1, n_hit, n_sweeps, 0);
+    rc = run_sweeps(L, beta0, beta1, n_hit, n_sweeps, 0, stats != nullptr);
     if (rc) return rc;
     if (stats) return read_stats(L, stats);
     return SU3HB_OK;
@@ -875,7 +857,7 @@ int su3hb_overrelax(su3hb_lattice *L, double beta0, double beta1, int n_sweeps, 
     if (rc) return rc;
     HIPCHK(hipSetDevice(L->device));
     if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
-    rc = run_sweeps(L, beta0, beta1, 0, n_sweeps, 0);  // n_hit 0: overrelaxation
+    rc = run_sweeps(L, beta0, beta1, 0, n_sweeps, 0, stats != nullptr);  // n_hit 0: overrelaxation
     if (rc) return rc;
     if (stats) return read_stats(L, stats);
     return SU3HB_OK;
@@ -892,9 +874,12 @@ int su3hb_sweep_measure(su3hb_lattice *L, double beta0, double beta1, int n_hit,
     HIPCHK(hipSetDevice(L->device));
     if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
     for (int done = 0; done < n_sweeps;) {
-        const int chunk = std::min<int>(int(kSeriesCap), n_sweeps - done);
-        HIPCHK(launch_counter_set(L->stream, L->d_cursor, 0));
-        rc = run_sweeps(L, beta0, beta1, n_hit, chunk, 1);
+        int chunk = std::min<int>(int(kSeriesCap), n_sweeps - done);
+        rc = ensure_meas(L, chunk, &chunk);
+        if (rc) return rc;
+        HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
+        rc = run_sweeps(L, beta0, beta1, n_hit, chunk, 1, stats != nullptr);
+        if (!rc) rc = finish_measure(L, beta0, beta1, chunk, L->d_series);
         if (rc) return rc;
         HIPCHK(hipMemcpyAsync(series + size_t(done) * 6, L->d_series, sizeof(double) * 6 * chunk,
                               hipMemcpyDeviceToHost, L->stream));
@@ -910,7 +895,7 @@ int su3hb_plaquette(su3hb_lattice *L, double beta0, double beta1, double out[6])
     if (!L || !out) return fail(SU3HB_EINVAL, "NULL argument");
     if (L->batch) return fail(SU3HB_EINVAL, "use su3hb_batch_plaquette for batches");
     HIPCHK(hipSetDevice(L->device));
-    int rc = enqueue_plaquette(L, L->stream, beta0, beta1, nullptr);
+    int rc = enqueue_plaquette(L, L->stream, beta0, beta1);
     if (rc) return rc;
     HIPCHK(hipMemcpyAsync(out, L->d_plaq, sizeof(double) * 6, hipMemcpyDeviceToHost, L->stream));
     HIPCHK(hipStreamSynchronize(L->stream));
@@ -989,7 +974,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
         if (it != g_tune_cache.end())
             return apply_launch(L, it->second.block, it->second.order, it->second.waves);
     }
-    // keep the state: links, sweep counter and statistics are restored below
+    // keep the state: links and sweep counter are restored below
     void *backup = nullptr;
     hipError_t e = hipMalloc(&backup, L->links_bytes);
     if (e != hipSuccess) return fail(SU3HB_ENOMEM, "autotune backup: %s", hipGetErrorString(e));
@@ -1022,8 +1007,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     const double b = L->batch ? 0.0 : 6.0;
     // single lattices are timed with the fused measurement (its parity-1
     // slices hold the staple snapshots in LDS, which decides the occupancy
-    // of some shapes); the series cursor is reset before every timed batch of
-    // at most 64 sweeps and after the tuning
+    // of some shapes)
     const int meas = fused_measure(L) ? 1 : 0;
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
@@ -1046,16 +1030,19 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
             return SU3HB_OK;
         }
         if (r) return r;
-        if (meas && (r = ensure_meas(L)) != SU3HB_OK) return r;
-        if (hipSuccess != launch_counter_set(L->stream, L->d_cursor, 0)) return fail(SU3HB_EHIP, "cursor");
-        if ((r = enqueue_sweep(L, L->stream, b, b, 8, meas)) != SU3HB_OK) return r;  // warm-up
+        int slots = 0;
+        if (meas && (r = ensure_meas(L, 1, &slots)) != SU3HB_OK) return r;
+        auto one_sweep = [&]() -> int {
+            if (meas && hipSuccess != launch_measure_begin(L->stream, L->d_sweep)) return fail(SU3HB_EHIP, "measure");
+            return enqueue_sweep(L, L->stream, b, b, 8, meas, false);
+        };
+        if ((r = one_sweep()) != SU3HB_OK) return r;  // warm-up
         int reps = min_reps;
         float ms = 0.f;
         for (;;) {
-            if (hipSuccess != launch_counter_set(L->stream, L->d_cursor, 0)) return fail(SU3HB_EHIP, "cursor");
             if (hipEventRecord(e0, L->stream) != hipSuccess) return fail(SU3HB_EHIP, "event");
             for (int k = 0; k < reps; ++k)
-                if ((r = enqueue_sweep(L, L->stream, b, b, 8, meas)) != SU3HB_OK) return r;
+                if ((r = one_sweep()) != SU3HB_OK) return r;
             if (hipEventRecord(e1, L->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
                 return fail(SU3HB_EHIP, "event");
             hipEventElapsedTime(&ms, e0, e1);
@@ -1098,8 +1085,6 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     hipEventDestroy(e1);
     HIPCHK(hipMemcpyAsync(L->links, backup, L->links_bytes, hipMemcpyDeviceToDevice, L->stream));
     HIPCHK(launch_counter_set(L->stream, L->d_sweep, uint32_t(sweep0)));
-    HIPCHK(launch_counter_set(L->stream, L->d_cursor, 0));
-    HIPCHK(launch_stats_zero(L->stream, L->d_stats));
     HIPCHK(hipStreamSynchronize(L->stream));
     L->sweep = sweep0;
     if (rc) return rc;
@@ -1122,20 +1107,27 @@ int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, i
     if (!rc) rc = check_sweep_room(L, n_sweeps);
     if (rc) return rc;
     HIPCHK(hipSetDevice(L->device));
-    if (measure && fused_measure(L)) {
-        rc = ensure_meas(L);
+    if (measure) {
+        int slots = 0;
+        rc = ensure_meas(L, 1, &slots);
         if (rc) return rc;
     }
     const size_t launches = size_t(n_sweeps) * (size_t(2 * L->nd) + (measure ? 1 : 0));
     rc = ensure_events(L, 2 * launches);
     if (rc) return rc;
-    if (measure) HIPCHK(launch_counter_set(L->stream, L->d_cursor, 0));
     size_t ev = 0;
     std::vector<int> kinds;
     kinds.reserve(launches);
     for (int sw = 0; sw < n_sweeps; ++sw) {
-        rc = enqueue_sweep(L, L->stream, beta0, beta1, n_hit, measure, &kinds, &ev);
+        if (measure) HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
+        rc = enqueue_sweep(L, L->stream, beta0, beta1, n_hit, measure, false, &kinds, &ev);
         if (rc) return rc;
+        if (!measure) continue;
+        HIPCHK(hipEventRecord(L->events[ev++], L->stream));
+        rc = finish_measure(L, beta0, beta1, 1, L->d_series + size_t(sw) * 6);
+        if (rc) return rc;
+        HIPCHK(hipEventRecord(L->events[ev++], L->stream));
+        kinds.push_back(1);
     }
     L->sweep += uint64_t(n_sweeps);
     HIPCHK(hipStreamSynchronize(L->stream));
@@ -1224,7 +1216,7 @@ int su3hb_batch_sweep(su3hb_batch *L, int n_hit, int n_sweeps, int mode, su3hb_s
     HIPCHK(hipSetDevice(L->device));
     if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
     if (mode == 0) {
-        rc = run_sweeps(L, 0.0, 0.0, n_hit, n_sweeps, 0);
+        rc = run_sweeps(L, 0.0, 0.0, n_hit, n_sweeps, 0, stats != nullptr);
         if (rc) return rc;
     } else if (n_sweeps > 0) {
         // one resident block per CU (as many as fit), slices separated by a
@@ -1234,7 +1226,7 @@ int su3hb_batch_sweep(su3hb_batch *L, int n_hit, int n_sweeps, int mode, su3hb_s
         HIPCHK(persistent_max_blocks(L->nd, L->prec, &per_cu));
         if (per_cu < 1) return fail(SU3HB_EUNSUPPORTED, "persistent kernel cannot be resident");
         const int blocks = int(std::min<uint64_t>(uint64_t(per_cu) * L->num_cus, L->pers_blocks));
-        UpdateArgs a = update_args(L, 0.0, 0.0, n_hit);
+        UpdateArgs a = update_args(L, 0.0, 0.0, n_hit, stats != nullptr);
         a.order = 0;
         a.persistent = 1;
         a.barrier = L->d_bar;
@@ -1263,7 +1255,7 @@ int su3hb_batch_plaquette(su3hb_batch *L, double *out, size_t n)
     if (!L || !L->batch || !out) return fail(SU3HB_EINVAL, "bad arguments");
     if (n != size_t(L->nrep) * 6) return fail(SU3HB_EINVAL, "n = %zu, expected 6 per replica", n);
     HIPCHK(hipSetDevice(L->device));
-    int rc = enqueue_plaquette(L, L->stream, 0.0, 0.0, nullptr);
+    int rc = enqueue_plaquette(L, L->stream, 0.0, 0.0);
     if (rc) return rc;
     HIPCHK(hipMemcpyAsync(out, L->d_plaq, sizeof(double) * n, hipMemcpyDeviceToHost, L->stream));
     HIPCHK(hipStreamSynchronize(L->stream));
@@ -1341,9 +1333,6 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     hipStream_t st = reinterpret_cast<hipStream_t>(p->hip_stream);
     RepDesc *d_rep = reinterpret_cast<RepDesc *>(base + kScrRep);
     uint32_t *d_sweep = reinterpret_cast<uint32_t *>(base + kScrSweep);
-    uint32_t *d_cursor = reinterpret_cast<uint32_t *>(base + kScrCursor);
-    double *d_plaq = reinterpret_cast<double *>(base + kScrPlaq);
-    StatSlot *d_stats = reinterpret_cast<StatSlot *>(base + kScrStats);
     double *d_meas = reinterpret_cast<double *>(base + kScrMeas);
 
     UpdateArgs a;
@@ -1357,7 +1346,6 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     a.beta1 = beta1;
     a.meas_classes = nc;
     a.sweep = d_sweep;
-    a.stats = d_stats;
     a.total_blocks = rep.upd_blocks;
     a.meas = series ? d_meas : nullptr;
     const dim3 grid((rep.upd_blocks + 7) / 8 * 8), block(kBlock);
@@ -1373,19 +1361,20 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     // set-up: no memset nodes (kernels clear what must start at zero)
     HIPCHK(launch_rep_set(st, rep, d_rep));
     HIPCHK(launch_counter_set(st, d_sweep, uint32_t(sweep0)));
-    HIPCHK(launch_counter_set(st, d_cursor, 0));
-    HIPCHK(launch_stats_zero(st, d_stats));
+    // measured sweeps in runs whose partial sums fit the scratch
+    const int run = series ? int(std::min<size_t>(size_t(n_sweeps), kScratchMeasDoubles / meas_doubles)) : n_sweeps;
     for (int sw = 0; sw < n_sweeps; ++sw) {
+        if (series && sw % run == 0) HIPCHK(launch_measure_begin(st, d_sweep));
         for (int par = 0; par < 2; ++par)
             for (int mu = 0; mu < p->nd; ++mu) {
                 a.parity = par;
                 a.mu = mu;
                 HIPCHK(launch_update(p->nd, p->precision, kDefaultWaves, grid, block, st, a));
             }
-        HIPCHK(launch_counter_add(st, d_sweep, 1));
-        if (series)
-            HIPCHK(launch_measure_finalize(st, d_meas, p->nd, rep.upd_blocks, nc, double(rep.V), int(rep.nlat), beta0,
-                                           beta1, d_plaq, series, d_cursor));
+        const int done = sw % run + 1;
+        if (series && (done == run || sw + 1 == n_sweeps))
+            HIPCHK(launch_measure_finalize(st, d_meas, done, p->nd, rep.upd_blocks, nc, double(rep.V), int(rep.nlat),
+                                           beta0, beta1, series + size_t(sw + 1 - done) * 6));
     }
     return SU3HB_OK;
 }

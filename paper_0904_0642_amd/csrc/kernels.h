@@ -24,15 +24,13 @@ hipError_t persistent_max_blocks(int D, int prec, int *blocks_per_cu);
 // plaquettes: per-block partial sums, then one block per replica finalises
 hipError_t launch_plaquette(int D, int prec, dim3 grid, dim3 block, hipStream_t st, const PlaqArgs &a);
 hipError_t launch_plaquette_finalize(hipStream_t st, const RepDesc *reps, int nrep, int D,
-                                     const double *partials, double *out, double *series,
-                                     uint32_t *series_cursor);
+                                     const double *partials, double *out);
 
-// fused measurement: sums the per-block plaquette class partials (nc = 1 for
-// one layer, 3 for two) the parity-1 update slices wrote, normalises like the
-// plaquette path
-hipError_t launch_measure_finalize(hipStream_t st, const double *meas, int D, uint32_t nblocks, int nc, double V,
-                                   int nlat, double beta0, double beta1, double *out, double *series,
-                                   uint32_t *cursor);
+// fused measurement of n sweeps: sums the per-block plaquette class partials
+// (nc = 1 for one layer, 3 for two) that the parity-1 update slices of each
+// sweep wrote, normalises like the plaquette path, into series (6 per sweep)
+hipError_t launch_measure_finalize(hipStream_t st, const double *meas, int n, int D, uint32_t nblocks, int nc,
+                                   double V, int nlat, double beta0, double beta1, double *series);
 
 // start configuration of one replica: mode 1 ordered, 2 Haar
 hipError_t launch_start(int D, int prec, hipStream_t st, void *links, const RepDesc *reps, int r,
@@ -56,6 +54,8 @@ hipError_t launch_stats_zero(hipStream_t st, StatSlot *slots);
 hipError_t launch_stats_reduce(hipStream_t st, const StatSlot *slots, StatSlot *out);
 hipError_t launch_counter_add(hipStream_t st, uint32_t *ctr, uint32_t add);
 hipError_t launch_counter_set(hipStream_t st, uint32_t *ctr, uint32_t value);
+// the counter's word 2 from its word 0: measured sweeps begin (kSweepWords)
+hipError_t launch_measure_begin(hipStream_t st, uint32_t *sweep);
 hipError_t launch_u32_zero(hipStream_t st, uint32_t *p, int n);
 hipError_t launch_u64_zero(hipStream_t st, unsigned long long *p, int n);
 

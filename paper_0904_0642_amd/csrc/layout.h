@@ -87,6 +87,17 @@ constexpr uint32_t kBarrierXcdTop = 3584;
 constexpr uint32_t kBarrierXcdRelease = 3712;
 constexpr uint32_t kBarrierSpinLimit = 1u << 22;
 
+// The sweep counter on the device: word 0 is the index of the next sweep,
+// which the parity-0 slices read; their last one copies it to word 1, which
+// the parity-1 slices read, and the last of those writes word 0 of the sweep
+// after.  No slice writes a word that it reads, so the counter needs no
+// launch of its own: a launch of one wave costs 4.4 us inside a replayed
+// graph, and so did adding up each sweep's plaquettes (5.7 us), now one launch
+// for all sweeps of a call (4^4 FP64-18, 20 measured sweeps: 2.46 -> 2.13 ms;
+// 16^4, 4 sweeps: 0.70 -> 0.64 ms).  Word 2 is the index of the first sweep of a measured
+// run: sweep i writes its partial sums at place i - word 2 of `meas`.
+constexpr int kSweepWords = 3;
+
 // Statistics slot, padded to its own 128-byte line.
 struct alignas(128) StatSlot {
     unsigned long long attempts[3];
@@ -115,10 +126,10 @@ struct UpdateArgs {
     int stage;                   // 1: each wave stages the U_mu links its planes nu = 0, 1 read in LDS
     uint32_t stage_r;            // staging halo: n_0 / 2 half-sites before and after a wave's 64
     double beta0, beta1;
-    const uint32_t *sweep;       // device sweep counter
-    StatSlot *stats;             // kStatSlots slots
+    uint32_t *sweep;             // device sweep counter, kSweepWords words
+    StatSlot *stats;             // kStatSlots slots, or null: no counters are kept
     uint32_t total_blocks;       // real blocks (grid may be padded to 8)
-    double *meas;                // fused plaquettes: [mu][total_blocks][meas_classes] partial sums, or null
+    double *meas;                // fused plaquettes: [sweep][mu][total_blocks][meas_classes] partial sums, or null
     int meas_classes;            // 1: one lattice layer; 3: two layers (classes by base layer and tags)
     int persistent;              // 1: logical blocks of the persistent partition
     uint32_t *barrier;           // persistent launches: kBarrierWords counters, zeroed before the launch

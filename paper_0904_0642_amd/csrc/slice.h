@@ -1,0 +1,40 @@
+// slice.h -- what the slice update kernels share: the guarded norm of a
+// projected SU(2) block, the place of a sweep's partial sums, the step of the
+// device's sweep counter.
+#pragma once
+
+#include "geometry.h"
+
+namespace su3hb {
+
+// 1/k for the norm k = sqrt(k2) of a projected SU(2) block; false for a
+// degenerate projection (k <= 1e-300), which no hit accepts.  Norms from
+// 2^-500 up take rsqrt_refined; smaller ones the exact square root, so the
+// degenerate test is the one of the definition.
+__device__ __forceinline__ bool inv_norm(double k2, double &ik)
+{
+    if (k2 >= 0x1p-1000) {
+        ik = rsqrt_refined(k2);
+        return true;
+    }
+    const double k = sqrt(k2);
+    if (!(k > 1e-300)) return false;
+    ik = 1.0 / k;
+    return true;
+}
+
+// The place of this sweep's partial sums (parity-1 slices).
+template <int D, int NC>
+__device__ __forceinline__ double *meas_of_sweep(const UpdateArgs &a, uint32_t sweep)
+{
+    return a.meas + size_t(sweep - a.sweep[2]) * (size_t(D) * a.total_blocks * NC);
+}
+
+// The sweep counter's step at the end of each parity (one thread per launch;
+// kSweepWords in layout.h).
+__device__ __forceinline__ void advance_sweep(const UpdateArgs &a, int D, uint32_t sweep)
+{
+    if (a.mu == D - 1 && blockIdx.x == 0 && threadIdx.x == 0) a.sweep[1 - a.parity] = sweep + uint32_t(a.parity);
+}
+
+}  // namespace su3hb

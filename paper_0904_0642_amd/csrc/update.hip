@@ -10,26 +10,10 @@
 // The links of one slice are independent (Sec. 2), so one thread owns one
 // link and the slice is one launch.
 
-#include "geometry.h"
 #include "kernels.h"
+#include "slice.h"
 
 namespace su3hb {
-
-// 1/k for the norm k = sqrt(k2) of a projected SU(2) block; false for a
-// degenerate projection (k <= 1e-300), which no hit accepts.  Norms from
-// 2^-500 up take rsqrt_refined; smaller ones the exact square root, so the
-// degenerate test is the one of the definition.
-__device__ __forceinline__ bool inv_norm(double k2, double &ik)
-{
-    if (k2 >= 0x1p-1000) {
-        ik = rsqrt_refined(k2);
-        return true;
-    }
-    const double k = sqrt(k2);
-    if (!(k > 1e-300)) return false;
-    ik = 1.0 / k;
-    return true;
-}
 
 // The logarithm table of log_unit, copied into LDS by every update kernel
 // before its first draw (fill_log_table: all threads of the block).
@@ -315,13 +299,16 @@ __device__ __forceinline__ void update_link(const UpdateArgs &a, const RepDesc &
     store_link<PREC>(uptr, Ud);
 }
 
-// Sum the per-thread counters over the block and add them to one slot; with
-// a fused measurement also store the block's NC plaquette class sums (plain
-// stores, one group per (direction, block), added up later in a fixed order).
-template <int NC>
-__device__ __forceinline__ void flush_stats(const UpdateArgs &a, uint32_t lb, int att[3], int acc[3], int upd,
-                                            double dtrace, double *plaq)
+// Sum the per-thread counters over the block and add them to one slot (when
+// the caller asked for them); with a fused measurement also store the block's
+// NC plaquette class sums (plain stores, one group per (direction, block),
+// added up later in a fixed order).
+template <int D, int NC>
+__device__ __forceinline__ void flush_stats(const UpdateArgs &a, uint32_t lb, uint32_t sweep, int att[3], int acc[3],
+                                            int upd, double dtrace, double *plaq)
 {
+    const bool measured = a.meas != nullptr && a.parity == 1;
+    if (a.stats == nullptr && !measured) return;
     int v[7] = {att[0], att[1], att[2], acc[0], acc[1], acc[2], upd};
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -351,17 +338,21 @@ __device__ __forceinline__ void flush_stats(const UpdateArgs &a, uint32_t lb, in
 #pragma unroll
             for (int c = 0; c < NC; ++c) plaq[c] += s_dbl[w][1 + c];
         }
-        StatSlot *sl = &a.stats[lb % kStatSlots];
+        if (a.stats != nullptr) {
+            StatSlot *sl = &a.stats[lb % kStatSlots];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            atomicAdd(&sl->attempts[i], (unsigned long long)v[i]);
-            atomicAdd(&sl->accepts[i], (unsigned long long)v[3 + i]);
+            for (int i = 0; i < 3; ++i) {
+                atomicAdd(&sl->attempts[i], (unsigned long long)v[i]);
+                atomicAdd(&sl->accepts[i], (unsigned long long)v[3 + i]);
+            }
+            atomicAdd(&sl->updates, (unsigned long long)v[6]);
+            unsafeAtomicAdd(&sl->dtrace, dtrace);
         }
-        atomicAdd(&sl->updates, (unsigned long long)v[6]);
-        unsafeAtomicAdd(&sl->dtrace, dtrace);
-        if (a.meas != nullptr && a.parity == 1 && lb < a.total_blocks)
+        if (measured && lb < a.total_blocks) {
+            double *m = meas_of_sweep<D, NC>(a, sweep) + (size_t(a.mu) * a.total_blocks + lb) * NC;
 #pragma unroll
-            for (int c = 0; c < NC; ++c) a.meas[(size_t(a.mu) * a.total_blocks + lb) * NC + c] = plaq[c];
+            for (int c = 0; c < NC; ++c) m[c] = plaq[c];
+        }
     }
     __syncthreads();  // the shared arrays are reused by the next block in a persistent loop
 }
@@ -442,7 +433,7 @@ __device__ __forceinline__ void process_block(const UpdateArgs &a, uint32_t lb, 
 #pragma unroll
     for (int c = 0; c < NC; ++c) plaq[c] = 0.0;
     block_links<D, PREC, NC>(a, lb, sweep, att, acc, upd, dtrace, plaq, lt_override);
-    flush_stats<NC>(a, lb, att, acc, upd, dtrace, plaq);
+    flush_stats<D, NC>(a, lb, sweep, att, acc, upd, dtrace, plaq);
 }
 
 // Logical block of hardware block b.  Hardware blocks are dealt round-robin
@@ -543,7 +534,9 @@ __global__ void __launch_bounds__(256, WAVES) update_kernel(UpdateArgs a)
         lt = int64_t(link_of_thread_4d(a, b));
     else
         lb = logical_block(a, b);
-    process_block<D, PREC, NC>(a, lb, *a.sweep, lt);
+    const uint32_t sweep = a.sweep[a.parity];
+    process_block<D, PREC, NC>(a, lb, sweep, lt);
+    advance_sweep(a, D, sweep);
 }
 
 // Grid barrier of a persistent launch (all blocks resident: cooperative
@@ -709,7 +702,7 @@ __global__ void __launch_bounds__(THREADS, persistent_waves(PREC)) update_persis
                     const uint32_t lb = first + (back ? n - 1u - j : j) * step;
                     block_links<D, PREC, 1>(b, lb, sweep0 + uint32_t(sw), att, acc, upd, dtrace, plaq);
                 }
-                flush_stats<1>(b, blockIdx.x, att, acc, upd, dtrace, plaq);
+                flush_stats<D, 1>(b, blockIdx.x, sweep0 + uint32_t(sw), att, acc, upd, dtrace, plaq);
                 if (!xcd_barrier(a.barrier, gen++, x, members, nxcd)) return;
             }
         }
@@ -734,7 +727,9 @@ template <int D, int PREC>
 static const void *update_fn(int waves, const UpdateArgs &a)
 {
     if (a.meas != nullptr && a.parity == 1 && a.meas_classes == 3)
-        return reinterpret_cast<const void *>(&update_kernel<D, PREC, kDefaultWaves, 3>);
+        // (FP32-12, D = 4: held to the 128 registers of 4 waves per SIMD)
+        return reinterpret_cast<const void *>(
+            &update_kernel<D, PREC, PREC == kFP32_12 && D == 4 ? 4 : kDefaultWaves, 3>);
     // parity-0 slices of a measured sweep measure nothing and use this kernel
     if (a.meas != nullptr && a.meas_classes != 1 && a.meas_classes != 3) return nullptr;
     if constexpr (D == 4) {
@@ -784,7 +779,7 @@ static hipError_t launch_update_t(int waves, dim3 grid, dim3 block, hipStream_t 
 }
 
 template <int D>
-static hipError_t launch_update_d(int prec, int waves, dim3 grid, dim3 block, hipStream_t st,
+hipError_t launch_update_d(int prec, int waves, dim3 grid, dim3 block, hipStream_t st,
                                   const UpdateArgs &a)
 {
     switch (prec) {
@@ -797,7 +792,7 @@ static hipError_t launch_update_d(int prec, int waves, dim3 grid, dim3 block, hi
 }
 
 template <int D>
-static hipError_t update_lds_d(int prec, int waves, dim3 block, const UpdateArgs &a, size_t *need, size_t *limit)
+hipError_t update_lds_d(int prec, int waves, dim3 block, const UpdateArgs &a, size_t *need, size_t *limit)
 {
     switch (prec) {
     case kFP64_18: return update_lds_t<D, kFP64_18>(waves, block, a, need, limit);
@@ -805,6 +800,49 @@ static hipError_t update_lds_d(int prec, int waves, dim3 block, const UpdateArgs
     case kFP32_12: return update_lds_t<D, kFP32_12>(waves, block, a, need, limit);
     case kFP64_12: return update_lds_t<D, kFP64_12>(waves, block, a, need, limit);
     default: return hipErrorInvalidValue;
+    }
+}
+
+template <int D>
+const void *persistent_fn_d(int prec)
+{
+    switch (prec) {
+    case kFP64_18: return reinterpret_cast<const void *>(&update_persistent_kernel<D, kFP64_18, kPersistentThreads>);
+    case kFP32_18: return reinterpret_cast<const void *>(&update_persistent_kernel<D, kFP32_18, kPersistentThreads>);
+    case kFP32_12: return reinterpret_cast<const void *>(&update_persistent_kernel<D, kFP32_12, kPersistentThreads>);
+    case kFP64_12: return reinterpret_cast<const void *>(&update_persistent_kernel<D, kFP64_12, kPersistentThreads>);
+    default: return nullptr;
+    }
+}
+
+// SU3HB_DIM: this object holds the kernels of one dimension (the build
+// compiles the file once for each); without it, the calls that choose among
+// them.
+#ifdef SU3HB_DIM
+template hipError_t launch_update_d<SU3HB_DIM>(int, int, dim3, dim3, hipStream_t, const UpdateArgs &);
+template hipError_t update_lds_d<SU3HB_DIM>(int, int, dim3, const UpdateArgs &, size_t *, size_t *);
+template const void *persistent_fn_d<SU3HB_DIM>(int);
+#else
+#define SU3HB_EXTERN(DD)                                                                                     \
+    extern template hipError_t launch_update_d<DD>(int, int, dim3, dim3, hipStream_t, const UpdateArgs &);   \
+    extern template hipError_t update_lds_d<DD>(int, int, dim3, const UpdateArgs &, size_t *, size_t *);     \
+    extern template const void *persistent_fn_d<DD>(int);
+SU3HB_EXTERN(2)
+SU3HB_EXTERN(3)
+SU3HB_EXTERN(4)
+SU3HB_EXTERN(5)
+SU3HB_EXTERN(6)
+#undef SU3HB_EXTERN
+
+static const void *persistent_fn(int D, int prec)
+{
+    switch (D) {
+    case 2: return persistent_fn_d<2>(prec);
+    case 3: return persistent_fn_d<3>(prec);
+    case 4: return persistent_fn_d<4>(prec);
+    case 5: return persistent_fn_d<5>(prec);
+    case 6: return persistent_fn_d<6>(prec);
+    default: return nullptr;
     }
 }
 
@@ -818,30 +856,6 @@ hipError_t update_lds(int D, int prec, int waves, dim3 block, const UpdateArgs &
     case 6: return update_lds_d<6>(prec, waves, block, a, need, limit);
     default: return hipErrorInvalidValue;
     }
-}
-
-static const void *persistent_fn(int D, int prec)
-{
-#define SU3HB_K(DD, PP) reinterpret_cast<const void *>(&update_persistent_kernel<DD, PP, kPersistentThreads>)
-#define SU3HB_P(DD)                                        \
-    case DD:                                               \
-        switch (prec) {                                    \
-        case kFP64_18: return SU3HB_K(DD, kFP64_18);       \
-        case kFP32_18: return SU3HB_K(DD, kFP32_18);       \
-        case kFP32_12: return SU3HB_K(DD, kFP32_12);       \
-        case kFP64_12: return SU3HB_K(DD, kFP64_12);       \
-        default: return nullptr;                           \
-        }
-    switch (D) {
-        SU3HB_P(2)
-        SU3HB_P(3)
-        SU3HB_P(4)
-        SU3HB_P(5)
-        SU3HB_P(6)
-    default: return nullptr;
-    }
-#undef SU3HB_P
-#undef SU3HB_K
 }
 
 hipError_t persistent_max_blocks(int D, int prec, int *blocks_per_cu)
@@ -873,5 +887,6 @@ hipError_t launch_update(int D, int prec, int waves, dim3 grid, dim3 block, hipS
     default: return hipErrorInvalidValue;
     }
 }
+#endif
 
 }  // namespace su3hb

@@ -1,0 +1,37 @@
+"""Measured sweeps: the partial sums of all sweeps of a call are added up
+together, the device's sweep counter is stepped by the slices themselves, and
+counters are kept only where they are asked for."""
+import numpy as np
+import pytest
+
+import paper_0904_0642_amd as su3hb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ext,nlat,mask,prec", [([4, 2], 1, 0, su3hb.FP64_18), ([6, 4, 4, 2], 1, 0, su3hb.FP32_12),
+                                                ([4, 6, 2, 4], 2, 0b0111, su3hb.FP64_12)])
+def test_calls_of_any_length_give_one_chain(ext, nlat, mask, prec):
+    # the same 35 sweeps in calls of 1, 2, 17 (more than the room kept at
+    # first) and 15, with and without counters, and in one call; identical
+    # sums, so identical bits
+    kw = dict(nlat=nlat, dlt_mask=mask, precision=prec, seed=3)
+    a, b, c = (su3hb.Lattice(ext, **kw) for _ in range(3))
+    one = a.sweep_measure(5.6, 6.0, n_sweeps=35)
+    parts = []
+    for k, n in enumerate((1, 2, 17, 15)):
+        if k % 2:
+            s, st = b.sweep_measure(5.6, 6.0, n_sweeps=n, stats=True)
+            assert st["link_updates"] == n * b.n_links
+            assert all(acc <= att for acc, att in zip(st["accepts"], st["attempts"])) and min(st["attempts"]) > 0
+        else:
+            s = b.sweep_measure(5.6, 6.0, n_sweeps=n)
+        parts.append(s)
+    assert np.array_equal(np.concatenate(parts), one, equal_nan=True)
+    _, timed = c.sweep_timed(5.6, 6.0, n_sweeps=35, measure=True)
+    assert np.array_equal(timed, one, equal_nan=True)
+    for g in (b, c):
+        assert np.array_equal(g.get_links(), a.get_links()) and g.get_state() == a.get_state()
+    # counters of a call hold that call only
+    a.sweep(5.6, 6.0, n_sweeps=2)
+    assert a.sweep(5.6, 6.0, n_sweeps=3, stats=True)["link_updates"] == 3 * a.n_links
