@@ -518,6 +518,17 @@ __global__ void measure_begin_kernel(uint32_t *sweep)
     if (threadIdx.x == 0) sweep[2] = sweep[0];
 }
 
+// n sweeps in one launch begin: its queue is empty, they count from word 2,
+// and the sweep after them is in word 0.
+__global__ void small_begin_kernel(uint32_t *sweep, uint32_t n, uint32_t *work)
+{
+    for (uint32_t i = threadIdx.x; i < kSmallWords; i += blockDim.x) work[i] = i == kSmallXcd ? kSmallNoXcd : 0u;
+    if (threadIdx.x != 0) return;
+    const uint32_t s = sweep[0];
+    sweep[2] = s;
+    sweep[0] = s + n;
+}
+
 __global__ void u32_zero_kernel(uint32_t *p, int n)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -570,6 +581,12 @@ hipError_t launch_counter_set(hipStream_t st, uint32_t *ctr, uint32_t value)
 hipError_t launch_measure_begin(hipStream_t st, uint32_t *sweep)
 {
     hipLaunchKernelGGL(measure_begin_kernel, dim3(1), dim3(64), 0, st, sweep);
+    return hipGetLastError();
+}
+
+hipError_t launch_small_begin(hipStream_t st, uint32_t *sweep, uint32_t n_sweeps, uint32_t *work)
+{
+    hipLaunchKernelGGL(small_begin_kernel, dim3(1), dim3(256), 0, st, sweep, n_sweeps, work);
     return hipGetLastError();
 }
 

@@ -88,6 +88,10 @@ struct su3hb_lattice {
     double *d_stage = nullptr;
     uint32_t *d_bar = nullptr;    // grid-barrier counters of persistent launches
     int block = 256, order = 1, waves = kDefaultWaves;
+    bool shape_set = false;       // by su3hb_set_launch or the tuner
+    uint32_t split_groups = 0;    // blocks of 16 links (split.h) in a slice
+    uint32_t *d_work = nullptr;   // queue of launches that hold whole sweeps
+    uint32_t *h_failed = nullptr; // host memory: such a launch gave up
     uint32_t upd_blocks = 0, plq_blocks = 0, pers_blocks = 0;
     bool use_graph = true;
     GraphCache graphs[kGraphSlots];
@@ -101,6 +105,7 @@ namespace {
 std::mutex g_tune_mu;
 struct Shape {
     int block, order, waves;
+    bool automatic;  // left to use_split
 };
 std::map<std::string, Shape> g_tune_cache;
 
@@ -120,7 +125,7 @@ void drop_graph(su3hb_lattice *L)
 void layout_reps(su3hb_lattice *L)
 {
     uint64_t off = 0;
-    uint32_t ub = 0, pb = 0, sb = 0;
+    uint32_t ub = 0, pb = 0, sb = 0, gb = 0;
     const int NE = elems_per_link(L->prec);
     for (auto &r : L->reps) {
         r.elem_offset = off;
@@ -140,7 +145,10 @@ void layout_reps(su3hb_lattice *L)
         r.pers_block0 = sb;
         r.pers_blocks = (r.nlat * r.Vh + kPersistentThreads - 1) / kPersistentThreads;
         sb += r.pers_blocks;
+        r.split_group0 = gb;
+        gb += (r.nlat * r.Vh + kSplitLinks - 1) / kSplitLinks;
     }
+    L->split_groups = gb;
     L->upd_blocks = ub;
     L->plq_blocks = pb;
     L->pers_blocks = sb;
@@ -209,6 +217,7 @@ int alloc_common(su3hb_lattice *L)
     HIPCHK(hipMalloc(&L->d_series, sizeof(double) * 6 * kSeriesCap));
     HIPCHK(hipMalloc(&L->d_maxdef, sizeof(unsigned long long)));
     HIPCHK(hipMalloc(&L->d_bar, sizeof(uint32_t) * kBarrierWords));
+    HIPCHK(hipMalloc(&L->d_work, sizeof(uint32_t) * kSmallWords));
     layout_reps(L);
     HIPCHK(hipMalloc(&L->d_partials, sizeof(double) * 5 * L->plq_blocks));
     int rc = upload_reps(L);
@@ -260,6 +269,8 @@ void destroy(su3hb_lattice *L)
     hipFree(L->d_maxdef);
     hipFree(L->d_stage);
     hipFree(L->d_bar);
+    hipFree(L->d_work);
+    hipHostFree(L->h_failed);
     if (L->cap) hipStreamDestroy(L->cap);
     delete L;
 }
@@ -349,6 +360,15 @@ int effective_order(const su3hb_lattice *L)
     return base_order(L) | (L->order & kOrderReverse) | (stage_applies(L) ? kOrderStage : 0);
 }
 
+// Slices that share every link's update between lanes and waves, and calls that
+// hold whole sweeps in one launch (the lines are drawn in layout.h): unless the
+// caller or the tuner chose a launch shape.
+bool use_split(const su3hb_lattice *L) { return !L->shape_set && L->split_groups <= kSplitGroups; }
+bool use_small(const su3hb_lattice *L) { return !L->shape_set && L->split_groups <= kSmallGroups; }
+
+// Blocks that write partial sums in a measured slice.
+uint32_t meas_blocks(const su3hb_lattice *L) { return use_split(L) ? L->split_groups : L->upd_blocks; }
+
 UpdateArgs update_args(const su3hb_lattice *L, double b0, double b1, int nhit, bool counters)
 {
     UpdateArgs a;
@@ -426,7 +446,7 @@ int meas_classes(const su3hb_lattice *L) { return L->reps[0].nlat == 2 ? 3 : 1; 
 // Doubles of partial sums that one measured sweep writes.
 size_t meas_doubles(const su3hb_lattice *L)
 {
-    return size_t(L->nd) * L->upd_blocks * size_t(meas_classes(L));
+    return size_t(L->nd) * meas_blocks(L) * size_t(meas_classes(L));
 }
 
 // Room for the partial sums of n sweeps, or of as many as kMeasBytes hold
@@ -463,8 +483,10 @@ int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nh
         a.meas = L->d_meas;
         a.meas_classes = meas_classes(L);
     }
+    const bool split = use_split(L);
+    if (split) a.total_blocks = L->split_groups;
     const dim3 grid = update_grid(L), block(L->block);
-    {
+    if (!split) {
         // the largest LDS request of the sweep (a measured parity-1 slice)
         // must fit one block's share of the compute unit
         UpdateArgs m = a;
@@ -481,7 +503,8 @@ int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nh
             a.mu = mu;
             a.reverse = (L->order & kOrderReverse) && ((p * L->nd + mu) & 1) ? 1 : 0;
             if (timed) HIPCHK(hipEventRecord(L->events[(*ev)++], st));
-            HIPCHK(launch_update(L->nd, L->prec, L->waves, grid, block, st, a));
+            if (split) HIPCHK(launch_update_split(L->nd, L->prec, st, a));
+            else HIPCHK(launch_update(L->nd, L->prec, L->waves, grid, block, st, a));
             if (timed) {
                 HIPCHK(hipEventRecord(L->events[(*ev)++], st));
                 timed->push_back(0);
@@ -494,7 +517,7 @@ int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nh
 // n rows of the series.
 int finish_measure(su3hb_lattice *L, double b0, double b1, int n, double *series)
 {
-    HIPCHK(launch_measure_finalize(L->stream, L->d_meas, n, L->nd, L->upd_blocks, meas_classes(L),
+    HIPCHK(launch_measure_finalize(L->stream, L->d_meas, n, L->nd, meas_blocks(L), meas_classes(L),
                                    double(L->reps[0].V), int(L->reps[0].nlat), b0, b1, series));
     return SU3HB_OK;
 }
@@ -553,11 +576,52 @@ int check_sweep_room(const su3hb_lattice *L, int n)
     return SU3HB_OK;
 }
 
+// n sweeps in launches that hold whole sweeps; the first one begins the
+// measurement.
+int run_small(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measure, bool counters)
+{
+    if (!L->h_failed) {
+        HIPCHK(hipHostMalloc(&L->h_failed, sizeof(uint32_t), 0));
+        *L->h_failed = 0;
+    }
+    SmallArgs s;
+    std::memset(&s, 0, sizeof s);
+    s.u = update_args(L, b0, b1, nhit, counters);
+    s.u.total_blocks = L->split_groups;
+    if (measure) {
+        s.u.meas = L->d_meas;
+        s.u.meas_classes = meas_classes(L);
+    }
+    s.per_slice = div_magic(L->split_groups);
+    s.work = L->d_work;
+    s.failed = L->h_failed;
+    const uint32_t per_sweep = 2u * uint32_t(L->nd) * L->split_groups;
+    const int most = measure ? n : std::max(1, int(std::min<uint32_t>(kSeriesCap, (1u << 30) / per_sweep)));
+    for (int done = 0; done < n;) {
+        const int k = std::min(most, n - done);
+        s.items = per_sweep * uint32_t(k);
+        HIPCHK(launch_small_begin(L->stream, L->d_sweep, uint32_t(k), L->d_work));
+        HIPCHK(launch_update_small(L->nd, L->prec, L->stream, s));
+        done += k;
+    }
+    return SU3HB_OK;
+}
+
+// After a synchronisation: whether a launch of whole sweeps gave up a wait.
+int check_small(const su3hb_lattice *L)
+{
+    if (L->h_failed && *static_cast<volatile uint32_t *>(L->h_failed))
+        return fail(SU3HB_EHIP, "a sweep waited past its limit; the links are not valid");
+    return SU3HB_OK;
+}
+
 int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measure, bool counters)
 {
     if (n <= 0) return SU3HB_OK;
     if (int rc = check_sweep_room(L, n)) return rc;
-    if (L->use_graph) {
+    if (use_small(L)) {
+        if (int rc = run_small(L, b0, b1, nhit, n, measure, counters)) return rc;
+    } else if (L->use_graph) {
         hipGraphExec_t exec = nullptr;
         int rc = get_graph(L, b0, b1, nhit, measure, counters, &exec);
         if (rc) return rc;
@@ -578,6 +642,7 @@ int read_stats(su3hb_lattice *L, su3hb_stats *out)
     HIPCHK(launch_stats_reduce(L->stream, L->d_stats, L->d_stats_out));
     HIPCHK(hipMemcpyAsync(&s, L->d_stats_out, sizeof s, hipMemcpyDeviceToHost, L->stream));
     HIPCHK(hipStreamSynchronize(L->stream));
+    if (int rc = check_small(L)) return rc;
     for (int i = 0; i < 3; ++i) {
         out->attempts[i] = s.attempts[i];
         out->accepts[i] = s.accepts[i];
@@ -622,7 +687,7 @@ int get_replica_links(su3hb_lattice *L, int r, double *host, size_t n)
                               hipMemcpyDeviceToHost, L->stream));
         HIPCHK(hipStreamSynchronize(L->stream));
     }
-    return SU3HB_OK;
+    return check_small(L);
 }
 
 int set_replica_links(su3hb_lattice *L, int r, const double *host, size_t n)
@@ -688,10 +753,12 @@ int apply_launch(su3hb_lattice *L, int block, int order, int waves)
         return fail(SU3HB_EINVAL, "waves = %d: 2, or 3 for D = 4, or 4 for D = 4 with FP32 links", waves);
     HIPCHK(hipStreamSynchronize(L->stream));
     drop_graph(L);
+    const bool old_set = L->shape_set;
     const int old_block = L->block, old_order = L->order, old_waves = L->waves;
     L->block = block;
     L->order = order;
     L->waves = waves;
+    L->shape_set = true;
     layout_reps(L);
     // a measured parity-1 slice asks for the most LDS: staple snapshots and,
     // when staging, the staging areas
@@ -707,12 +774,20 @@ int apply_launch(su3hb_lattice *L, int block, int order, int waves)
         L->block = old_block;
         L->order = old_order;
         L->waves = old_waves;
+        L->shape_set = old_set;
         layout_reps(L);
         if (e != hipSuccess) return fail(SU3HB_EHIP, "LDS query: %s", hipGetErrorString(e));
         return fail(SU3HB_EUNSUPPORTED, "launch (%d, %d, %d) needs %zu bytes of LDS per block, the device allows %zu",
                     block, order, waves, need, limit);
     }
     return upload_reps(L);
+}
+
+int apply_shape(su3hb_lattice *L, const Shape &s)
+{
+    if (int rc = apply_launch(L, s.block, s.order, s.waves)) return rc;
+    L->shape_set = !s.automatic;
+    return SU3HB_OK;
 }
 
 int ensure_events(su3hb_lattice *L, size_t n)
@@ -818,6 +893,7 @@ int su3hb_init_lattice(su3hb_lattice **out, const su3hb_params *p)
             L->block = it->second.block;
             L->order = it->second.order;
             L->waves = it->second.waves;
+            L->shape_set = !it->second.automatic;
         }
     }
     rc = adopt_or_alloc_links(L, p->device_links, p->device_bytes);
@@ -877,13 +953,14 @@ int su3hb_sweep_measure(su3hb_lattice *L, double beta0, double beta1, int n_hit,
         int chunk = std::min<int>(int(kSeriesCap), n_sweeps - done);
         rc = ensure_meas(L, chunk, &chunk);
         if (rc) return rc;
-        HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
+        if (!use_small(L)) HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
         rc = run_sweeps(L, beta0, beta1, n_hit, chunk, 1, stats != nullptr);
         if (!rc) rc = finish_measure(L, beta0, beta1, chunk, L->d_series);
         if (rc) return rc;
         HIPCHK(hipMemcpyAsync(series + size_t(done) * 6, L->d_series, sizeof(double) * 6 * chunk,
                               hipMemcpyDeviceToHost, L->stream));
         HIPCHK(hipStreamSynchronize(L->stream));
+        if ((rc = check_small(L)) != SU3HB_OK) return rc;
         done += chunk;
     }
     if (stats) return read_stats(L, stats);
@@ -899,7 +976,7 @@ int su3hb_plaquette(su3hb_lattice *L, double beta0, double beta1, double out[6])
     if (rc) return rc;
     HIPCHK(hipMemcpyAsync(out, L->d_plaq, sizeof(double) * 6, hipMemcpyDeviceToHost, L->stream));
     HIPCHK(hipStreamSynchronize(L->stream));
-    return SU3HB_OK;
+    return check_small(L);
 }
 
 int su3hb_get_links(const su3hb_lattice *Lc, double *host, size_t n)
@@ -972,7 +1049,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(key);
         if (it != g_tune_cache.end())
-            return apply_launch(L, it->second.block, it->second.order, it->second.waves);
+            return apply_shape(L, it->second);
     }
     // keep the state: links and sweep counter are restored below
     void *backup = nullptr;
@@ -988,6 +1065,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     // D = 4; orders 2 to 6 only where they apply (otherwise they would repeat
     // another order), orders 3, 5 and 6 only with more than one wave per block
     std::vector<Shape> cands;
+    if (L->split_groups <= kSplitGroups) cands.push_back(Shape{256, 1, kDefaultWaves, true});
     for (int waves : {2, 3, 4}) {
         if (waves >= 3 && L->nd != 4) continue;
         if (waves == 4 && !is_fp32(L->prec)) continue;
@@ -996,11 +1074,11 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
                 if ((order == 2 || order == 4) && !slab_order_ok(L, block)) continue;
                 if (order == 7 && !tile4_order_ok(L, block)) continue;
                 if (is_cube_order(order) && (block == 64 || !cube_order_ok(L, block, order))) continue;
-                cands.push_back(Shape{block, order, waves});
-                cands.push_back(Shape{block, order | kOrderReverse, waves});
+                cands.push_back(Shape{block, order, waves, false});
+                cands.push_back(Shape{block, order | kOrderReverse, waves, false});
                 if (order != 7 && !L->batch && L->reps[0].nlat == 1) {
-                    cands.push_back(Shape{block, order | kOrderStage, waves});
-                    cands.push_back(Shape{block, order | kOrderReverse | kOrderStage, waves});
+                    cands.push_back(Shape{block, order | kOrderStage, waves, false});
+                    cands.push_back(Shape{block, order | kOrderReverse | kOrderStage, waves, false});
                 }
             }
     }
@@ -1024,7 +1102,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     // most 64 sweeps); ms per sweep, or a negative value for a shape whose
     // LDS does not fit (not a candidate)
     auto time_cand = [&](size_t i, int min_reps, double target_ms, float *out) -> int {
-        int r = apply_launch(L, cands[i].block, cands[i].order, cands[i].waves);
+        int r = apply_shape(L, cands[i]);
         if (r == SU3HB_EUNSUPPORTED) {
             *out = -1.f;
             return SU3HB_OK;
@@ -1092,7 +1170,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
         std::lock_guard<std::mutex> lk(g_tune_mu);
         g_tune_cache[key] = cands[best_i];
     }
-    return apply_launch(L, cands[best_i].block, cands[best_i].order, cands[best_i].waves);
+    return apply_shape(L, cands[best_i]);
 }
 
 int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, int n_sweeps, int measure,
@@ -1190,6 +1268,7 @@ int su3hb_batch_create(su3hb_batch **out, int nd, const su3hb_replica_desc *reps
             L->block = it->second.block;
             L->order = it->second.order;
             L->waves = it->second.waves;
+            L->shape_set = !it->second.automatic;
         }
     }
     int rc = adopt_or_alloc_links(L, nullptr, 0);
@@ -1259,7 +1338,7 @@ int su3hb_batch_plaquette(su3hb_batch *L, double *out, size_t n)
     if (rc) return rc;
     HIPCHK(hipMemcpyAsync(out, L->d_plaq, sizeof(double) * n, hipMemcpyDeviceToHost, L->stream));
     HIPCHK(hipStreamSynchronize(L->stream));
-    return SU3HB_OK;
+    return check_small(L);
 }
 
 int su3hb_batch_get_links(su3hb_batch *L, int replica, double *host, size_t n)
@@ -1319,7 +1398,11 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     rep.upd_block0 = 0;
     rep.upd_blocks = (rep.nlat * rep.Vh + kBlock - 1) / kBlock;
     const int nc = p->nlat == 2 ? 3 : 1;
-    const size_t meas_doubles = size_t(p->nd) * rep.upd_blocks * size_t(nc);
+    // small slices as in a handle whose launch shape was not set
+    const uint32_t groups = (rep.nlat * rep.Vh + kSplitLinks - 1) / kSplitLinks;
+    const bool split = groups <= kSplitGroups;
+    const uint32_t blocks = split ? groups : rep.upd_blocks;
+    const size_t meas_doubles = size_t(p->nd) * blocks * size_t(nc);
     if (series && meas_doubles > kScratchMeasDoubles)
         return fail(SU3HB_EINVAL,
                     "lattice too large for the static scratch: the measurement needs %zu partial sums, the scratch "
@@ -1346,10 +1429,10 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     a.beta1 = beta1;
     a.meas_classes = nc;
     a.sweep = d_sweep;
-    a.total_blocks = rep.upd_blocks;
+    a.total_blocks = blocks;
     a.meas = series ? d_meas : nullptr;
     const dim3 grid((rep.upd_blocks + 7) / 8 * 8), block(kBlock);
-    {
+    if (!split) {
         UpdateArgs m = a;
         m.parity = 1;
         size_t need = 0, limit = 0;
@@ -1369,11 +1452,12 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
             for (int mu = 0; mu < p->nd; ++mu) {
                 a.parity = par;
                 a.mu = mu;
-                HIPCHK(launch_update(p->nd, p->precision, kDefaultWaves, grid, block, st, a));
+                if (split) HIPCHK(launch_update_split(p->nd, p->precision, st, a));
+                else HIPCHK(launch_update(p->nd, p->precision, kDefaultWaves, grid, block, st, a));
             }
         const int done = sw % run + 1;
         if (series && (done == run || sw + 1 == n_sweeps))
-            HIPCHK(launch_measure_finalize(st, d_meas, done, p->nd, rep.upd_blocks, nc, double(rep.V), int(rep.nlat),
+            HIPCHK(launch_measure_finalize(st, d_meas, done, p->nd, blocks, nc, double(rep.V), int(rep.nlat),
                                            beta0, beta1, series + size_t(sw + 1 - done) * 6));
     }
     return SU3HB_OK;

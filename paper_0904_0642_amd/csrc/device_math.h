@@ -446,6 +446,7 @@ struct Store<kFP64_12> {
 struct LinkRef {
     char *slab;   // first byte of the (layer, direction, parity) slab
     uint32_t h;   // half-lattice index of the link
+    char *links;  // first byte of the link buffer
 };
 
 // Bytes of one stored link and the address of packet 0 of link h: tile
@@ -479,37 +480,50 @@ typedef double nt_double2 __attribute__((ext_vector_type(2)));
 typedef float nt_float4 __attribute__((ext_vector_type(4)));
 typedef float nt_float2 __attribute__((ext_vector_type(2)));
 
-// A packet read with the normal or (NT) the non-temporal cache policy.
-template <typename V, bool NT>
-__device__ __forceinline__ V read_packet(const char *p)
+// Cache policies of a link's load.  kFresh passes the compute unit's L1 by
+// (the links of a launch that holds several slices change under it); it needs
+// a link buffer below 2 GiB.
+constexpr int kNormal = 0, kNonTemporal = 1, kFresh = 2;
+
+template <typename V, int POLICY>
+__device__ __forceinline__ V read_packet(const LinkRef &r, const char *p)
 {
-    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
-    else return *reinterpret_cast<const V *>(p);
+    if constexpr (POLICY == kNonTemporal) {
+        return __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
+    } else if constexpr (POLICY == kFresh) {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(r.links, 0, 0x7FFFFFFF, 0x00027000);
+        const int off = int(p - r.links);
+        constexpr int kDeviceScope = 16;  // the sc1 bit of the cache policy: not from the L1
+        if constexpr (sizeof(V) == 16)
+            return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, kDeviceScope));
+        else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, kDeviceScope));
+    } else {
+        return *reinterpret_cast<const V *>(p);
+    }
 }
 
 // complex element e of a link
-template <int PREC, bool NT = false>
+template <int PREC, int POLICY = kNormal>
 __device__ __forceinline__ cx<typename Store<PREC>::real> load_elem(const LinkRef &r, int e)
 {
     using R = typename Store<PREC>::real;
     if constexpr (sizeof(R) == 8) {
-        const nt_double2 v = read_packet<nt_double2, NT>(packet_ptr<PREC>(r, e));
+        const nt_double2 v = read_packet<nt_double2, POLICY>(r, packet_ptr<PREC>(r, e));
         return cx<R>{v.x, v.y};
     } else {
         constexpr int NP = Store<PREC>::NE / 2;
         if (e >= 2 * NP) {
-            const nt_float2 v = read_packet<nt_float2, NT>(tail_ptr<PREC>(r));
+            const nt_float2 v = read_packet<nt_float2, POLICY>(r, tail_ptr<PREC>(r));
             return cx<R>{v.x, v.y};
         }
-        const nt_float2 v = read_packet<nt_float2, NT>(packet_ptr<PREC>(r, e >> 1) + (e & 1) * 8);
+        const nt_float2 v = read_packet<nt_float2, POLICY>(r, packet_ptr<PREC>(r, e >> 1) + (e & 1) * 8);
         return cx<R>{v.x, v.y};
     }
 }
 
 // The NE stored elements of a link (row 2 of 12-real storage left unset);
-// NT: the non-temporal policy, for a link no other thread of the launch
-// reads.
-template <int PREC, bool NT = false>
+// kNonTemporal for a link no other thread of the launch reads.
+template <int PREC, int POLICY = kNormal>
 __device__ __forceinline__ mat3<typename Store<PREC>::real> load_stored(const LinkRef &r)
 {
     using R = typename Store<PREC>::real;
@@ -517,25 +531,25 @@ __device__ __forceinline__ mat3<typename Store<PREC>::real> load_stored(const Li
     mat3<R> m;
     if constexpr (sizeof(R) == 8) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e) m.e[e / 3][e % 3] = load_elem<PREC, NT>(r, e);
+        for (int e = 0; e < NE; ++e) m.e[e / 3][e % 3] = load_elem<PREC, POLICY>(r, e);
     } else {
         constexpr int NP = NE / 2;
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
-            const nt_float4 v = read_packet<nt_float4, NT>(packet_ptr<PREC>(r, j));
+            const nt_float4 v = read_packet<nt_float4, POLICY>(r, packet_ptr<PREC>(r, j));
             m.e[(2 * j) / 3][(2 * j) % 3] = cx<R>{v.x, v.y};
             m.e[(2 * j + 1) / 3][(2 * j + 1) % 3] = cx<R>{v.z, v.w};
         }
-        if constexpr (NE & 1) m.e[2][2] = load_elem<PREC, NT>(r, NE - 1);
+        if constexpr (NE & 1) m.e[2][2] = load_elem<PREC, POLICY>(r, NE - 1);
     }
     return m;
 }
 
 // A whole link.
-template <int PREC, bool NT = false>
+template <int PREC, int POLICY = kNormal>
 __device__ __forceinline__ mat3<typename Store<PREC>::real> load_link(const LinkRef &r)
 {
-    mat3<typename Store<PREC>::real> m = load_stored<PREC, NT>(r);
+    mat3<typename Store<PREC>::real> m = load_stored<PREC, POLICY>(r);
     if constexpr (Store<PREC>::NE == 6) third_row(m);
     return m;
 }
@@ -544,7 +558,15 @@ __device__ __forceinline__ mat3<typename Store<PREC>::real> load_link(const Link
 // the stores take the non-temporal policy and leave L2 to the neighbour
 // lines that other threads of the slice read again.
 
-template <int PREC>
+// A store that keeps the non-temporal policy, or (NT false) the normal one.
+template <bool NT, typename V>
+__device__ __forceinline__ void write_packet(const V &v, char *p)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
+    else *reinterpret_cast<V *>(p) = v;
+}
+
+template <int PREC, bool NT = true>
 __device__ __forceinline__ void store_link(const LinkRef &r, const mat3<double> &m)
 {
     using R = typename Store<PREC>::real;
@@ -552,19 +574,16 @@ __device__ __forceinline__ void store_link(const LinkRef &r, const mat3<double> 
     if constexpr (sizeof(R) == 8) {
 #pragma unroll
         for (int e = 0; e < NE; ++e)
-            __builtin_nontemporal_store(nt_double2{m.e[e / 3][e % 3].re, m.e[e / 3][e % 3].im},
-                                        reinterpret_cast<nt_double2 *>(packet_ptr<PREC>(r, e)));
+            write_packet<NT>(nt_double2{m.e[e / 3][e % 3].re, m.e[e / 3][e % 3].im}, packet_ptr<PREC>(r, e));
     } else {
         constexpr int NP = NE / 2;
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             const cx<double> a = m.e[(2 * j) / 3][(2 * j) % 3], b = m.e[(2 * j + 1) / 3][(2 * j + 1) % 3];
-            __builtin_nontemporal_store(nt_float4{float(a.re), float(a.im), float(b.re), float(b.im)},
-                                        reinterpret_cast<nt_float4 *>(packet_ptr<PREC>(r, j)));
+            write_packet<NT>(nt_float4{float(a.re), float(a.im), float(b.re), float(b.im)}, packet_ptr<PREC>(r, j));
         }
         if constexpr (NE & 1)
-            __builtin_nontemporal_store(nt_float2{float(m.e[2][2].re), float(m.e[2][2].im)},
-                                        reinterpret_cast<nt_float2 *>(tail_ptr<PREC>(r)));
+            write_packet<NT>(nt_float2{float(m.e[2][2].re), float(m.e[2][2].im)}, tail_ptr<PREC>(r));
     }
 }
 
@@ -585,18 +604,18 @@ __device__ __forceinline__ mat3<typename Store<PREC>::real> stored_form_r(const 
 
 // Rows 0 and 1 of a link (row 2 left unset): the first six stored elements
 // of every storage form.
-template <int PREC>
+template <int PREC, int POLICY = kNormal>
 __device__ __forceinline__ mat3<typename Store<PREC>::real> load_rows01(const LinkRef &r)
 {
     using R = typename Store<PREC>::real;
     mat3<R> m;
     if constexpr (sizeof(R) == 8) {
 #pragma unroll
-        for (int e = 0; e < 6; ++e) m.e[e / 3][e % 3] = load_elem<PREC>(r, e);
+        for (int e = 0; e < 6; ++e) m.e[e / 3][e % 3] = load_elem<PREC, POLICY>(r, e);
     } else {
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const nt_float4 v = read_packet<nt_float4, false>(packet_ptr<PREC>(r, j));
+            const nt_float4 v = read_packet<nt_float4, POLICY>(r, packet_ptr<PREC>(r, j));
             m.e[(2 * j) / 3][(2 * j) % 3] = cx<R>{v.x, v.y};
             m.e[(2 * j + 1) / 3][(2 * j + 1) % 3] = cx<R>{v.z, v.w};
         }

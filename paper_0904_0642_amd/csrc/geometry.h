@@ -8,12 +8,16 @@
 namespace su3hb {
 
 // Block partitions of the replicas: per-slice update launches, plaquette
-// launches, persistent launches.
-enum BlockKind { kUpdateBlocks = 0, kPlaquetteBlocks = 1, kPersistentBlocks = 2 };
+// launches, persistent launches, launches that share a link's update between
+// lanes (split.h).
+enum BlockKind { kUpdateBlocks = 0, kPlaquetteBlocks = 1, kPersistentBlocks = 2, kSplitBlocks = 3 };
 
 __device__ __forceinline__ uint32_t first_block(const RepDesc &r, int kind)
 {
-    return kind == kPlaquetteBlocks ? r.plq_block0 : kind == kPersistentBlocks ? r.pers_block0 : r.upd_block0;
+    return kind == kPlaquetteBlocks    ? r.plq_block0
+           : kind == kPersistentBlocks ? r.pers_block0
+           : kind == kSplitBlocks      ? r.split_group0
+                                       : r.upd_block0;
 }
 
 // Find the replica owning logical block lb: largest r with first[r] <= lb.
@@ -124,7 +128,8 @@ __device__ __forceinline__ LinkRef link_ref(void *links, const RepDesc &rep, uin
     constexpr size_t kElemBytes = sizeof(typename Store<PREC>::real) * 2;
     constexpr int NE = Store<PREC>::NE;
     const size_t slab = size_t((layer * D + uint32_t(dir)) * 2u + uint32_t(par)) * NE * rep.Vhp;
-    return LinkRef{reinterpret_cast<char *>(links) + (rep.elem_offset + slab) * kElemBytes, s >> 1};
+    return LinkRef{reinterpret_cast<char *>(links) + (rep.elem_offset + slab) * kElemBytes, s >> 1,
+                   reinterpret_cast<char *>(links)};
 }
 
 }  // namespace su3hb

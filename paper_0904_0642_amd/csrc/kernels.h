@@ -12,6 +12,15 @@ namespace su3hb {
 hipError_t launch_update(int D, int prec, int waves, dim3 grid, dim3 block, hipStream_t st,
                          const UpdateArgs &a);
 
+// the same slice with every link's update shared by lanes and waves
+// (split.h); a.total_blocks counts blocks of kSplitLinks links
+hipError_t launch_update_split(int D, int prec, hipStream_t st, const UpdateArgs &a);
+
+// whole sweeps of a small lattice or batch in one launch, after
+// launch_small_begin for the same number of sweeps
+hipError_t launch_update_small(int D, int prec, hipStream_t st, const SmallArgs &s);
+hipError_t launch_small_begin(hipStream_t st, uint32_t *sweep, uint32_t n_sweeps, uint32_t *work);
+
 // LDS one block of such a launch needs (static + dynamic) and the device's
 // per-block limit; the caller refuses launches that would not fit
 hipError_t update_lds(int D, int prec, int waves, dim3 block, const UpdateArgs &a, size_t *need, size_t *limit);

@@ -63,6 +63,7 @@ struct RepDesc {
     uint32_t plq_spt;        // plaquettes per thread in the plaquette launch
     uint32_t pers_block0;    // first block in a persistent launch (kPersistentThreads links per block)
     uint32_t pers_blocks;
+    uint32_t split_group0;   // first block in a launch that shares links between lanes (kSplitLinks links per block)
     DivMagic div[kMaxD - 1];  // division by n0 / 2 (entry 0) and by n_i (entry i, 0 < i < D - 1)
 };
 
@@ -97,6 +98,17 @@ constexpr uint32_t kBarrierSpinLimit = 1u << 22;
 // 16^4, 4 sweeps: 0.70 -> 0.64 ms).  Word 2 is the index of the first sweep of a measured
 // run: sweep i writes its partial sums at place i - word 2 of `meas`.
 constexpr int kSweepWords = 3;
+
+// Launches that share a link's update between lanes and waves (split.h): links
+// of a block; blocks ("groups") of a slice up to which the library takes them
+// by itself.  Time of a slice, one thread per link -> shared, FP64-18 / FP32-12:
+// 2048 links 14.9 -> 6.9 / 13.1 -> 6.4 us, 8192 links 15.6 -> 8.0 / 13.5 ->
+// 6.9 us, 24576 links 17.6 -> 13.6 / 13.3 -> 9.5 us, 32768 links 18.2 -> 16.7 /
+// 13.3 -> 11.1 us.  The shared form does twice the work per link, so where the
+// other fills the chip it loses (51840 links: 20.4 and 13.9 us one thread per
+// link).
+constexpr uint32_t kSplitLinks = 16;
+constexpr uint32_t kSplitGroups = 2048;
 
 // Statistics slot, padded to its own 128-byte line.
 struct alignas(128) StatSlot {
@@ -133,6 +145,24 @@ struct UpdateArgs {
     int meas_classes;            // 1: one lattice layer; 3: two layers (classes by base layer and tags)
     int persistent;              // 1: logical blocks of the persistent partition
     uint32_t *barrier;           // persistent launches: kBarrierWords counters, zeroed before the launch
+};
+
+// Whole sweeps in one launch (small lattices): the next ticket, the XCD that
+// works and, for every group of 16 links, the slices it has done; cleared
+// before the launch.  Up to 64 groups an XCD gives each its block (two per
+// compute unit in FP64); with two rounds of blocks a slice takes longer than
+// launched by itself (2048 links, FP64-18: 9.9 us against 6.9 us).
+constexpr uint32_t kSmallGroups = 64;
+constexpr uint32_t kSmallTicket = 0, kSmallXcd = 32, kSmallDone = 64, kSmallWords = kSmallDone + kSmallGroups;
+constexpr uint32_t kSmallNoXcd = 0xFFFFFFFFu;
+constexpr uint32_t kSmallSpinLimit = 1u << 24;
+
+struct SmallArgs {
+    UpdateArgs u;                // total_blocks: groups of a slice
+    uint32_t items;              // 2 D n_sweeps total_blocks, below 2^31
+    DivMagic per_slice;          // division by total_blocks
+    uint32_t *work;              // kSmallWords words
+    uint32_t *failed;            // host memory: set to 1 by a wait past its limit
 };
 
 struct PlaqArgs {

@@ -37,4 +37,19 @@ __device__ __forceinline__ void advance_sweep(const UpdateArgs &a, int D, uint32
     if (a.mu == D - 1 && blockIdx.x == 0 && threadIdx.x == 0) a.sweep[1 - a.parity] = sweep + uint32_t(a.parity);
 }
 
+// Between a wave's LDS writes and its lanes' reads of them: the wave's LDS
+// operations complete in order.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// XCD of the calling wave (hardware register XCC_ID, 4 bits).
+__device__ __forceinline__ uint32_t xcc_id()
+{
+    return __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (kBarrierXcds - 1u);
+}
+
 }  // namespace su3hb

@@ -265,7 +265,7 @@ __device__ __forceinline__ void update_link(const UpdateArgs &a, const RepDesc &
 
     // heatbath in the storage precision (FP64 for the draw, see su2_heatbath)
     const LinkRef uptr = link_ref<D, PREC>(a.links, rep, layer, mu, p, x.s);
-    mat3<R> U = load_link<PREC, true>(uptr);   // no other thread of the slice reads U
+    mat3<R> U = load_link<PREC, kNonTemporal>(uptr);   // no other thread of the slice reads U
     mat3<R> W = mul_nn(U, A);   // A is not needed past this point
     const double tr_old = double(W.e[0][0].re) + double(W.e[1][1].re) + double(W.e[2][2].re);
 
@@ -575,12 +575,6 @@ __device__ __forceinline__ bool grid_barrier(uint32_t *bar, uint32_t gen)
     }
     __syncthreads();
     return s_ok != 0;
-}
-
-// XCD of the calling wave (hardware register XCC_ID, 4 bits).
-__device__ __forceinline__ uint32_t xcc_id()
-{
-    return __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (kBarrierXcds - 1u);
 }
 
 // Wait until *w reaches target (agent-scope loads); false when the abort
