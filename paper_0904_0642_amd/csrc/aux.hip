@@ -108,6 +108,65 @@ __global__ void __launch_bounds__(256) plaquette_kernel(PlaqArgs a)
         for (int i = 0; i < 5; ++i) a.partials[size_t(lb) * 5 + i] = v[i];
 }
 
+// One thread per site: all its planes one after another, so that a link comes
+// from the memory side once and from L2 for its other planes.  A wave takes 64
+// consecutive half-lattice indices of one parity, the next wave the other
+// parity of the same ones; XCD k takes a contiguous run of blocks.  The loops
+// over the planes stay loops: unrolled, every plane's loads are hoisted.  Per
+// plane of the lattice (plaquette_kernel) every link crossed the memory side
+// D - 1 times: 32^4 FP64-12 330 -> 160 us.
+template <int D, int PREC>
+__global__ void __launch_bounds__(256, 2) plaquette_site_kernel(PlaqArgs a)
+{
+    using R = typename Store<PREC>::real;
+    const uint32_t per = (a.total_blocks + 7u) >> 3, lb = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    if (lb >= a.total_blocks) return;
+    double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    const int r = a.nrep == 1 ? 0 : find_replica(a.reps, a.nrep, lb, kPlaquetteBlocks);
+    const RepDesc &rep = a.reps[r];
+    const uint32_t glued = rep.nlat == 2 ? rep.glued : 0u;
+    const double beta0 = a.use_rep_beta ? rep.beta0 : a.beta0;
+    const double beta1 = a.use_rep_beta ? rep.beta1 : a.beta1;
+    void *links = const_cast<void *>(a.links);
+    const uint32_t tiles = rep.Vhp / kTile, waves = rep.nlat * 2u * tiles;
+    const uint32_t w0 = ((lb - rep.plq_block0) * rep.plq_spt) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    for (uint32_t j = 0; j < rep.plq_spt; ++j) {
+        const uint32_t w = w0 + j * (blockDim.x >> 6);
+        if (w >= waves) break;
+        const uint32_t layer = w >= 2u * tiles ? 1u : 0u, wl = w - layer * 2u * tiles;
+        const int p = int(wl & 1u), q = 1 - p;
+        const uint32_t h = (wl >> 1) * kTile + (threadIdx.x & 63u);
+        if (h >= rep.Vh) continue;
+        Site<D> x;
+        x.template from_half<true>(rep, h, p, layer);
+#pragma unroll 1
+        for (int mu = 0; mu < D - 1; ++mu) {
+            const Step fm = step_fwd<D>(rep, x, mu, glued);
+            const uint32_t s_pm = x.s + uint32_t(fm.ds), l_pm = layer ^ fm.flip;
+            const mat3<R> umu = load_link<PREC>(link_ref<D, PREC>(links, rep, layer, mu, p, x.s));
+#pragma unroll 1
+            for (int nu = mu + 1; nu < D; ++nu) {
+                const Step fn = step_fwd<D>(rep, x, nu, glued);
+                const uint32_t s_pn = x.s + uint32_t(fn.ds), l_pn = layer ^ fn.flip;
+                const mat3<R> b = load_link<PREC>(link_ref<D, PREC>(links, rep, l_pm, nu, q, s_pm));
+                const mat3<R> c = load_link<PREC>(link_ref<D, PREC>(links, rep, layer, nu, p, x.s));
+                const mat3<R> d = load_link<PREC>(link_ref<D, PREC>(links, rep, l_pn, mu, q, s_pn));
+                const double P = re_tr_na(mul_nn(widen<double>(umu), widen<double>(b)),
+                                          mul_nn(widen<double>(c), widen<double>(d))) *
+                                 (1.0 / 3.0);
+                if (nu == D - 1) v[1] += P; else v[0] += P;
+                if (layer == 0) v[2] += P; else v[3] += P;
+                const uint32_t tags = layer + l_pm + l_pn + layer;
+                v[4] += (tags == 0 ? beta0 : beta1) * P;
+            }
+        }
+    }
+    block_sum<5>(v);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < 5; ++i) a.partials[size_t(lb) * 5 + i] = v[i];
+}
+
 // Fused measurement: meas[mu][b][c] holds the block sums of (1/3) Re Tr U_p
 // over the planes (nu, mu), nu < mu, written by the parity-1 update slices,
 // in nc classes: nc = 1 for one layer; nc = 3 for two layers (0: base site in
@@ -205,7 +264,8 @@ __global__ void __launch_bounds__(256) plaquette_finalize_kernel(const RepDesc *
 template <int D, int PREC>
 static hipError_t launch_plaquette_t(dim3 g, dim3 b, hipStream_t st, const PlaqArgs &a)
 {
-    hipLaunchKernelGGL((plaquette_kernel<D, PREC>), g, b, 0, st, a);
+    if (a.by_site) hipLaunchKernelGGL((plaquette_site_kernel<D, PREC>), dim3((g.x + 7) / 8 * 8), b, 0, st, a);
+    else hipLaunchKernelGGL((plaquette_kernel<D, PREC>), g, b, 0, st, a);
     return hipGetLastError();
 }
 

@@ -44,6 +44,10 @@ int fail(int code, const char *fmt, ...)
     } while (0)
 
 constexpr int kPlaqBlock = 256;
+// Sites from which the plaquette launch gives each thread a site instead of a
+// (site, plane): 16^4 FP64-18 46 -> 42 us a call and FP32-18 38 -> 39 us, 20^4 100
+// -> 68 and 63 -> 54 us, 32^4 513 -> 342 and 277 -> 191 us; 12^4 31 -> 38 us.
+constexpr uint64_t kPlaqBySite = uint64_t(1) << 16;
 constexpr uint32_t kSeriesCap = 4096;
 constexpr size_t kStageBytes = size_t(256) << 20;
 constexpr size_t kMeasBytes = size_t(64) << 20;  // partial sums kept before they are added up
@@ -89,6 +93,7 @@ struct su3hb_lattice {
     uint32_t *d_bar = nullptr;    // grid-barrier counters of persistent launches
     int block = 256, order = 1, waves = kDefaultWaves;
     bool shape_set = false;       // by su3hb_set_launch or the tuner
+    bool plq_by_site = false;     // plaquette launches: one thread per site
     uint32_t split_groups = 0;    // blocks of 16 links (split.h) in a slice
     uint32_t *d_work = nullptr;   // queue of launches that hold whole sweeps
     uint32_t *h_failed = nullptr; // host memory: such a launch gave up
@@ -124,7 +129,9 @@ void drop_graph(su3hb_lattice *L)
 // Block tables and offsets of every replica for the current launch shape.
 void layout_reps(su3hb_lattice *L)
 {
-    uint64_t off = 0;
+    uint64_t off = 0, sites = 0;
+    for (auto &r : L->reps) sites += uint64_t(r.nlat) * r.V;
+    L->plq_by_site = sites >= kPlaqBySite;
     uint32_t ub = 0, pb = 0, sb = 0, gb = 0;
     const int NE = elems_per_link(L->prec);
     for (auto &r : L->reps) {
@@ -133,10 +140,11 @@ void layout_reps(su3hb_lattice *L)
         r.upd_block0 = ub;
         r.upd_blocks = (r.nlat * r.Vh + L->block - 1) / L->block;
         ub += r.upd_blocks;
-        // one plaquette thread item per (site, plane); a few items per thread
-        // keep the partial sums to about 4096 blocks per lattice for the
-        // finalize pass
-        const uint64_t nitem = uint64_t(r.nlat) * r.V * uint64_t(L->nd * (L->nd - 1) / 2);
+        // one plaquette thread item per (site, plane), or per site (places of
+        // whole tiles); a few items per thread keep the partial sums to about
+        // 4096 blocks per lattice for the finalize pass
+        const uint64_t nitem = L->plq_by_site ? uint64_t(r.nlat) * 2 * r.Vhp
+                                              : uint64_t(r.nlat) * r.V * uint64_t(L->nd * (L->nd - 1) / 2);
         r.plq_spt = uint32_t(std::min<uint64_t>(16, std::max<uint64_t>(1, nitem / (uint64_t(kPlaqBlock) * 4096u))));
         r.plq_block0 = pb;
         const uint64_t per_block = uint64_t(kPlaqBlock) * r.plq_spt;
@@ -431,6 +439,7 @@ int enqueue_plaquette(su3hb_lattice *L, hipStream_t st, double b0, double b1)
     pa.use_rep_beta = L->batch ? 1 : 0;
     pa.partials = L->d_partials;
     pa.total_blocks = L->plq_blocks;
+    pa.by_site = L->plq_by_site;
     HIPCHK(launch_plaquette(L->nd, L->prec, dim3(L->plq_blocks), dim3(kPlaqBlock), st, pa));
     HIPCHK(launch_plaquette_finalize(st, L->d_reps, L->nrep, L->nd, L->d_partials, L->d_plaq));
     return SU3HB_OK;

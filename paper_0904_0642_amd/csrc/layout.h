@@ -60,7 +60,7 @@ struct RepDesc {
     uint32_t upd_blocks;     // blocks of this replica in an update launch
     uint32_t plq_block0;     // first block in a plaquette launch
     uint32_t plq_blocks;
-    uint32_t plq_spt;        // plaquettes per thread in the plaquette launch
+    uint32_t plq_spt;        // plaquettes (or sites) per thread in the plaquette launch
     uint32_t pers_block0;    // first block in a persistent launch (kPersistentThreads links per block)
     uint32_t pers_blocks;
     uint32_t split_group0;   // first block in a launch that shares links between lanes (kSplitLinks links per block)
@@ -173,6 +173,7 @@ struct PlaqArgs {
     int use_rep_beta;
     double *partials;            // [block][5]
     uint32_t total_blocks;
+    int by_site;                 // 1: one thread per site; 0: one per (site, plane)
 };
 
 constexpr int kDefaultWaves = 2;  // update kernels for D = 4 also exist for 3 (and, FP32, 4) waves/SIMD
