@@ -91,7 +91,7 @@ struct su3hb_lattice {
     unsigned long long *d_maxdef = nullptr;
     double *d_stage = nullptr;
     uint32_t *d_bar = nullptr;    // grid-barrier counters of persistent launches
-    int block = 256, order = 1, waves = kDefaultWaves;
+    int block = 256, order = 1, waves = kDefaultWaves;  // default_shape
     bool shape_set = false;       // by su3hb_set_launch or the tuner
     bool plq_by_site = false;     // plaquette launches: one thread per site
     uint32_t split_groups = 0;    // blocks of 16 links (split.h) in a slice
@@ -106,6 +106,13 @@ struct su3hb_lattice {
 };
 
 namespace {
+
+// Flag added to an order: alternate slices walk every XCD's blocks backwards.
+constexpr int kOrderReverse = 8;
+// Flag added to an order: every wave stages the U_mu links that its planes
+// nu = 0, 1 read in LDS (single-layer lattices outside batches, orders 0 to
+// 6, which give each wave 64 consecutive half-lattice indices).
+constexpr int kOrderStage = 16;
 
 std::mutex g_tune_mu;
 struct Shape {
@@ -124,6 +131,29 @@ void drop_slot(GraphCache &g)
 void drop_graph(su3hb_lattice *L)
 {
     for (auto &g : L->graphs) drop_slot(g);
+}
+
+// The shape of lattices and batches for which none is set: where it applies,
+// XCD slabs with the waves of a block along x_{D-2}, else XCD runs, and
+// alternate slices walked backwards, so that a slice begins on what the one
+// before read last; D = 4 FP32 18-real links at 3 waves per SIMD (the kernel
+// needs 128 registers then).  Microseconds a sweep, against runs walked
+// forwards at 2 waves: 48^4 FP64-18 6850 -> 5730, FP64-12 5290 -> 4320, FP32-18
+// 3310 -> 2840, FP32-12 2450 -> 2240; 32^4 FP64-18 1190 -> 1090, FP32-18 594 -> 529;
+// 24^3x64 FP32-18 490 -> 462; batch of 128 FP32-18 996 -> 911; 18x30x26x22 within
+// 2 %.  From D = 5 the slabs gain nothing and the waves along x_{D-2} cost FP32
+// links 1 % (8^6 FP32-18 365 against 369 us).
+Shape default_shape(int nd, int prec)
+{
+    return Shape{256, (nd <= 4 ? 6 : 1) | kOrderReverse, nd == 4 && prec == kFP32_18 ? 3 : kDefaultWaves, true};
+}
+
+void take_shape(su3hb_lattice *L, const Shape &s)
+{
+    L->block = s.block;
+    L->order = s.order;
+    L->waves = s.waves;
+    L->shape_set = !s.automatic;
 }
 
 // Block tables and offsets of every replica for the current launch shape.
@@ -340,13 +370,6 @@ bool tile4_order_ok(const su3hb_lattice *L, int block)
     const uint32_t nw = uint32_t(block) / 64u;
     return (uint32_t(r.n[0]) / 2u) % 8u == 0 && uint32_t(r.n[2]) % (2u * nw) == 0 && uint32_t(r.n[3]) % 16u == 0;
 }
-
-// Flag added to an order: alternate slices walk every XCD's blocks backwards.
-constexpr int kOrderReverse = 8;
-// Flag added to an order: every wave stages the U_mu links that its planes
-// nu = 0, 1 read in LDS (single-layer lattices outside batches, orders 0 to
-// 6, which give each wave 64 consecutive half-lattice indices).
-constexpr int kOrderStage = 16;
 
 // Block order in effect, without the flags.
 int base_order(const su3hb_lattice *L)
@@ -898,12 +921,7 @@ int su3hb_init_lattice(su3hb_lattice **out, const su3hb_params *p)
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(tune_key(L));
-        if (it != g_tune_cache.end()) {
-            L->block = it->second.block;
-            L->order = it->second.order;
-            L->waves = it->second.waves;
-            L->shape_set = !it->second.automatic;
-        }
+        take_shape(L, it != g_tune_cache.end() ? it->second : default_shape(L->nd, L->prec));
     }
     rc = adopt_or_alloc_links(L, p->device_links, p->device_bytes);
     if (!rc) rc = alloc_common(L);
@@ -1074,7 +1092,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     // D = 4; orders 2 to 6 only where they apply (otherwise they would repeat
     // another order), orders 3, 5 and 6 only with more than one wave per block
     std::vector<Shape> cands;
-    if (L->split_groups <= kSplitGroups) cands.push_back(Shape{256, 1, kDefaultWaves, true});
+    if (L->split_groups <= kSplitGroups) cands.push_back(default_shape(L->nd, L->prec));
     for (int waves : {2, 3, 4}) {
         if (waves >= 3 && L->nd != 4) continue;
         if (waves == 4 && !is_fp32(L->prec)) continue;
@@ -1273,12 +1291,7 @@ int su3hb_batch_create(su3hb_batch **out, int nd, const su3hb_replica_desc *reps
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(tune_key(L));
-        if (it != g_tune_cache.end()) {
-            L->block = it->second.block;
-            L->order = it->second.order;
-            L->waves = it->second.waves;
-            L->shape_set = !it->second.automatic;
-        }
+        take_shape(L, it != g_tune_cache.end() ? it->second : default_shape(L->nd, L->prec));
     }
     int rc = adopt_or_alloc_links(L, nullptr, 0);
     if (!rc) rc = alloc_common(L);
