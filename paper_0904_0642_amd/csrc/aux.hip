@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(256, 2) plaquette_site_kernel(PlaqArgs a)
 // layer 1).  One block per sweep adds them up in a fixed order.
 __global__ void __launch_bounds__(1024) measure_finalize_kernel(const double *meas, int D, uint32_t nblocks, int nc,
                                                                  double V, int nlat, double beta0, double beta1,
-                                                                 double *series)
+                                                                 double *series, uint32_t *sweep)
 {
     meas += size_t(blockIdx.x) * D * nblocks * nc;
     double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // [spacelike, timelike] x class
@@ -208,29 +208,17 @@ __global__ void __launch_bounds__(1024) measure_finalize_kernel(const double *me
         for (int w = 1; w < int(blockDim.x >> 6); ++w)
 #pragma unroll
             for (int i = 0; i < 6; ++i) v[i] += sh[w][i];
-        const double nV = double(nlat) * V;
-        const double nspace = nV * (D - 1) * (D - 2) / 2.0, ntime = nV * (D - 1);
-        const double nlayer = V * D * (D - 1) / 2.0;
-        const double nan = __builtin_nan("");
-        const double space = v[0] + v[1] + v[2], time = v[3] + v[4] + v[5];
-        const double t0 = v[0] + v[3], t1 = v[1] + v[4], t2 = v[2] + v[5];
-        double o[6];
-        o[0] = (space + time) / (nspace + ntime);
-        o[1] = nspace > 0 ? space / nspace : nan;
-        o[2] = time / ntime;
-        o[3] = (t0 + t1) / nlayer;
-        o[4] = nlat == 2 ? t2 / nlayer : nan;
-        o[5] = beta0 * t0 + beta1 * (t1 + t2);
-        for (int i = 0; i < 6; ++i) series[size_t(blockIdx.x) * 6 + i] = o[i];
+        plaquette_row(v, D, V, nlat, beta0, beta1, series + size_t(blockIdx.x) * 6);
+        if (blockIdx.x == 0) sweep[2] = 0u;
     }
 }
 
 hipError_t launch_measure_finalize(hipStream_t st, const double *meas, int n, int D, uint32_t nblocks, int nc,
-                                   double V, int nlat, double beta0, double beta1, double *series)
+                                   double V, int nlat, double beta0, double beta1, double *series, uint32_t *sweep)
 {
     if (nc != 1 && nc != 3) return hipErrorInvalidValue;
     hipLaunchKernelGGL(measure_finalize_kernel, dim3(n), dim3(1024), 0, st, meas, D, nblocks, nc, V, nlat, beta0,
-                       beta1, series);
+                       beta1, series, sweep);
     return hipGetLastError();
 }
 
@@ -534,7 +522,7 @@ __global__ void stats_zero_kernel(StatSlot *slots)
     s.dtrace = 0.0;
 }
 
-__global__ void stats_reduce_kernel(const StatSlot *slots, StatSlot *out)
+__global__ void stats_reduce_kernel(StatSlot *slots, StatSlot *out)
 {
     __shared__ unsigned long long si[kStatSlots][7];
     __shared__ double sd[kStatSlots];
@@ -545,6 +533,7 @@ __global__ void stats_reduce_kernel(const StatSlot *slots, StatSlot *out)
     }
     si[t][6] = slots[t].updates;
     sd[t] = slots[t].dtrace;
+    slots[t] = StatSlot{};  // empty for the next call
     __syncthreads();
     for (int w = kStatSlots / 2; w > 0; w >>= 1) {
         if (t < w) {
@@ -575,18 +564,7 @@ __global__ void counter_set_kernel(uint32_t *ctr, uint32_t value)
 
 __global__ void measure_begin_kernel(uint32_t *sweep)
 {
-    if (threadIdx.x == 0) sweep[2] = sweep[0];
-}
-
-// n sweeps in one launch begin: its queue is empty, they count from word 2,
-// and the sweep after them is in word 0.
-__global__ void small_begin_kernel(uint32_t *sweep, uint32_t n, uint32_t *work)
-{
-    for (uint32_t i = threadIdx.x; i < kSmallWords; i += blockDim.x) work[i] = i == kSmallXcd ? kSmallNoXcd : 0u;
-    if (threadIdx.x != 0) return;
-    const uint32_t s = sweep[0];
-    sweep[2] = s;
-    sweep[0] = s + n;
+    if (threadIdx.x == 0) sweep[2] = 0u;
 }
 
 __global__ void u32_zero_kernel(uint32_t *p, int n)
@@ -620,7 +598,7 @@ hipError_t launch_stats_zero(hipStream_t st, StatSlot *slots)
     return hipGetLastError();
 }
 
-hipError_t launch_stats_reduce(hipStream_t st, const StatSlot *slots, StatSlot *out)
+hipError_t launch_stats_reduce(hipStream_t st, StatSlot *slots, StatSlot *out)
 {
     hipLaunchKernelGGL(stats_reduce_kernel, dim3(1), dim3(kStatSlots), 0, st, slots, out);
     return hipGetLastError();
@@ -641,12 +619,6 @@ hipError_t launch_counter_set(hipStream_t st, uint32_t *ctr, uint32_t value)
 hipError_t launch_measure_begin(hipStream_t st, uint32_t *sweep)
 {
     hipLaunchKernelGGL(measure_begin_kernel, dim3(1), dim3(64), 0, st, sweep);
-    return hipGetLastError();
-}
-
-hipError_t launch_small_begin(hipStream_t st, uint32_t *sweep, uint32_t n_sweeps, uint32_t *work)
-{
-    hipLaunchKernelGGL(small_begin_kernel, dim3(1), dim3(256), 0, st, sweep, n_sweeps, work);
     return hipGetLastError();
 }
 

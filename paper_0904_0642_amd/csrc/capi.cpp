@@ -72,6 +72,7 @@ struct su3hb_lattice {
     int nd = 0, prec = 0, nrep = 0;
     bool batch = false;
     std::vector<RepDesc> reps;
+    void *d_tables = nullptr;     // the tables and accumulators below
     RepDesc *d_reps = nullptr;
     void *links = nullptr;
     size_t links_bytes = 0;
@@ -82,12 +83,18 @@ struct su3hb_lattice {
     uint64_t sweep = 0;
     uint64_t seed = 0;
     StatSlot *d_stats = nullptr;
-    StatSlot *d_stats_out = nullptr;
     double *d_partials = nullptr;
     double *d_meas = nullptr;     // fused measurement partials, [sweep][D][update blocks][classes]
     size_t meas_cap = 0;
-    double *d_plaq = nullptr;
-    double *d_series = nullptr;
+    // what calls return, written by the kernels straight into host memory: a
+    // copy of a few numbers back cost 8 to 10 us a call
+    struct Results {
+        double series[6 * kSeriesCap];
+        StatSlot stats;
+        uint32_t failed;         // a launch of whole sweeps gave up a wait
+    } *host = nullptr;
+    double *host_plaq = nullptr;  // 6 per replica
+    bool stats_dirty = true;      // the slots hold counts that no call has read
     unsigned long long *d_maxdef = nullptr;
     double *d_stage = nullptr;
     uint32_t *d_bar = nullptr;    // grid-barrier counters of persistent launches
@@ -95,8 +102,8 @@ struct su3hb_lattice {
     bool shape_set = false;       // by su3hb_set_launch or the tuner
     bool plq_by_site = false;     // plaquette launches: one thread per site
     uint32_t split_groups = 0;    // blocks of 16 links (split.h) in a slice
-    uint32_t *d_work = nullptr;   // queue of launches that hold whole sweeps
-    uint32_t *h_failed = nullptr; // host memory: such a launch gave up
+    uint32_t *d_work = nullptr;   // queues of launches that hold whole sweeps
+    uint32_t small_launches = 0;  // such launches so far
     uint32_t upd_blocks = 0, plq_blocks = 0, pers_blocks = 0;
     bool use_graph = true;
     GraphCache graphs[kGraphSlots];
@@ -242,26 +249,37 @@ RepDesc make_rep(int nd, const int *ext, int nlat, unsigned glued, int lat2test,
 
 int alloc_common(su3hb_lattice *L)
 {
-    hipDeviceProp_t prop;
     HIPCHK(hipGetDevice(&L->device));
-    HIPCHK(hipGetDeviceProperties(&prop, L->device));
-    L->num_cus = prop.multiProcessorCount;
+    HIPCHK(hipDeviceGetAttribute(&L->num_cus, hipDeviceAttributeMultiprocessorCount, L->device));
     HIPCHK(hipStreamCreateWithFlags(&L->cap, hipStreamNonBlocking));
-    HIPCHK(hipMalloc(&L->d_reps, sizeof(RepDesc) * L->reps.size()));
-    HIPCHK(hipMalloc(&L->d_sweep, sizeof(uint32_t) * kSweepWords));
-    HIPCHK(hipMalloc(&L->d_stats, sizeof(StatSlot) * kStatSlots));
-    HIPCHK(hipMalloc(&L->d_stats_out, sizeof(StatSlot)));
-    HIPCHK(hipMalloc(&L->d_plaq, sizeof(double) * 6 * L->reps.size()));
-    HIPCHK(hipMalloc(&L->d_series, sizeof(double) * 6 * kSeriesCap));
-    HIPCHK(hipMalloc(&L->d_maxdef, sizeof(unsigned long long)));
-    HIPCHK(hipMalloc(&L->d_bar, sizeof(uint32_t) * kBarrierWords));
-    HIPCHK(hipMalloc(&L->d_work, sizeof(uint32_t) * kSmallWords));
+    HIPCHK(hipHostMalloc(&L->host, sizeof(*L->host) + sizeof(double) * 6 * L->reps.size(), 0));
+    L->host->failed = 0;
+    L->host_plaq = reinterpret_cast<double *>(L->host + 1);
     layout_reps(L);
-    HIPCHK(hipMalloc(&L->d_partials, sizeof(double) * 5 * L->plq_blocks));
+    // the device's tables and accumulators: one allocation, places of 256 bytes
+    size_t bytes = 0;
+    auto place = [&](size_t n) {
+        const size_t at = bytes;
+        bytes += (n + 255) / 256 * 256;
+        return at;
+    };
+    const size_t reps = place(sizeof(RepDesc) * L->reps.size()), sweep = place(sizeof(uint32_t) * kSweepWords),
+                 stats = place(sizeof(StatSlot) * kStatSlots), maxdef = place(sizeof(unsigned long long)),
+                 bar = place(sizeof(uint32_t) * kBarrierWords),
+                 work = place(sizeof(uint32_t) * kSmallWords * kSmallQueues),
+                 partials = place(sizeof(double) * 5 * L->plq_blocks);
+    HIPCHK(hipMalloc(&L->d_tables, bytes));
+    char *base = static_cast<char *>(L->d_tables);
+    L->d_reps = reinterpret_cast<RepDesc *>(base + reps);
+    L->d_sweep = reinterpret_cast<uint32_t *>(base + sweep);
+    L->d_stats = reinterpret_cast<StatSlot *>(base + stats);
+    L->d_maxdef = reinterpret_cast<unsigned long long *>(base + maxdef);
+    L->d_bar = reinterpret_cast<uint32_t *>(base + bar);
+    L->d_work = reinterpret_cast<uint32_t *>(base + work);
+    L->d_partials = reinterpret_cast<double *>(base + partials);
     int rc = upload_reps(L);
     if (rc) return rc;
-    HIPCHK(launch_counter_set(L->stream, L->d_sweep, 0));
-    HIPCHK(launch_stats_zero(L->stream, L->d_stats));
+    HIPCHK(launch_u32_zero(L->stream, L->d_sweep, kSweepWords));
     return SU3HB_OK;
 }
 
@@ -296,19 +314,10 @@ void destroy(su3hb_lattice *L)
     drop_graph(L);
     for (auto e : L->events) hipEventDestroy(e);
     if (L->owns_links && L->links) hipFree(L->links);
-    hipFree(L->d_reps);
-    hipFree(L->d_sweep);
-    hipFree(L->d_stats);
-    hipFree(L->d_stats_out);
-    hipFree(L->d_partials);
+    hipFree(L->d_tables);
     hipFree(L->d_meas);
-    hipFree(L->d_plaq);
-    hipFree(L->d_series);
-    hipFree(L->d_maxdef);
     hipFree(L->d_stage);
-    hipFree(L->d_bar);
-    hipFree(L->d_work);
-    hipHostFree(L->h_failed);
+    hipHostFree(L->host);
     if (L->cap) hipStreamDestroy(L->cap);
     delete L;
 }
@@ -464,7 +473,7 @@ int enqueue_plaquette(su3hb_lattice *L, hipStream_t st, double b0, double b1)
     pa.total_blocks = L->plq_blocks;
     pa.by_site = L->plq_by_site;
     HIPCHK(launch_plaquette(L->nd, L->prec, dim3(L->plq_blocks), dim3(kPlaqBlock), st, pa));
-    HIPCHK(launch_plaquette_finalize(st, L->d_reps, L->nrep, L->nd, L->d_partials, L->d_plaq));
+    HIPCHK(launch_plaquette_finalize(st, L->d_reps, L->nrep, L->nd, L->d_partials, L->host_plaq));
     return SU3HB_OK;
 }
 
@@ -545,12 +554,12 @@ int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nh
     return SU3HB_OK;
 }
 
-// The plaquettes of the n measured sweeps since launch_measure_begin, into
-// n rows of the series.
+// The plaquettes of the n measured sweeps since the last of these, into n rows
+// of the series.
 int finish_measure(su3hb_lattice *L, double b0, double b1, int n, double *series)
 {
     HIPCHK(launch_measure_finalize(L->stream, L->d_meas, n, L->nd, meas_blocks(L), meas_classes(L),
-                                   double(L->reps[0].V), int(L->reps[0].nlat), b0, b1, series));
+                                   double(L->reps[0].V), int(L->reps[0].nlat), b0, b1, series, L->d_sweep));
     return SU3HB_OK;
 }
 
@@ -608,14 +617,11 @@ int check_sweep_room(const su3hb_lattice *L, int n)
     return SU3HB_OK;
 }
 
-// n sweeps in launches that hold whole sweeps; the first one begins the
-// measurement.
+// n sweeps in launches that hold whole sweeps; measured ones in a single
+// launch, which writes the series too (32^2, 6 measured sweeps: a launch before
+// and one after it and a copy made the call 210 us instead of 190).
 int run_small(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measure, bool counters)
 {
-    if (!L->h_failed) {
-        HIPCHK(hipHostMalloc(&L->h_failed, sizeof(uint32_t), 0));
-        *L->h_failed = 0;
-    }
     SmallArgs s;
     std::memset(&s, 0, sizeof s);
     s.u = update_args(L, b0, b1, nhit, counters);
@@ -625,14 +631,21 @@ int run_small(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measu
         s.u.meas_classes = meas_classes(L);
     }
     s.per_slice = div_magic(L->split_groups);
-    s.work = L->d_work;
-    s.failed = L->h_failed;
+    s.V = double(L->reps[0].V);
+    s.nlat = int(L->reps[0].nlat);
+    s.series = L->host->series;
+    s.failed = &L->host->failed;
     const uint32_t per_sweep = 2u * uint32_t(L->nd) * L->split_groups;
     const int most = measure ? n : std::max(1, int(std::min<uint32_t>(kSeriesCap, (1u << 30) / per_sweep)));
     for (int done = 0; done < n;) {
         const int k = std::min(most, n - done);
         s.items = per_sweep * uint32_t(k);
-        HIPCHK(launch_small_begin(L->stream, L->d_sweep, uint32_t(k), L->d_work));
+        s.sweep0 = uint32_t(L->sweep + uint64_t(done));
+        s.sweeps = uint32_t(k);
+        // a queue of its own for every launch; all are cleared once in a round
+        const uint32_t queue = L->small_launches++ % kSmallQueues;
+        if (queue == 0) HIPCHK(launch_u32_zero(L->stream, L->d_work, int(kSmallWords * kSmallQueues)));
+        s.work = L->d_work + queue * kSmallWords;
         HIPCHK(launch_update_small(L->nd, L->prec, L->stream, s));
         done += k;
     }
@@ -642,7 +655,7 @@ int run_small(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measu
 // After a synchronisation: whether a launch of whole sweeps gave up a wait.
 int check_small(const su3hb_lattice *L)
 {
-    if (L->h_failed && *static_cast<volatile uint32_t *>(L->h_failed))
+    if (*static_cast<volatile uint32_t *>(&L->host->failed))
         return fail(SU3HB_EHIP, "a sweep waited past its limit; the links are not valid");
     return SU3HB_OK;
 }
@@ -668,13 +681,22 @@ int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int meas
     return SU3HB_OK;
 }
 
+// A call that counts begins: the slots are empty unless a call failed between
+// counting and reading.
+int begin_stats(su3hb_lattice *L)
+{
+    if (L->stats_dirty) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
+    L->stats_dirty = true;
+    return SU3HB_OK;
+}
+
 int read_stats(su3hb_lattice *L, su3hb_stats *out)
 {
-    StatSlot s;
-    HIPCHK(launch_stats_reduce(L->stream, L->d_stats, L->d_stats_out));
-    HIPCHK(hipMemcpyAsync(&s, L->d_stats_out, sizeof s, hipMemcpyDeviceToHost, L->stream));
+    HIPCHK(launch_stats_reduce(L->stream, L->d_stats, &L->host->stats));
     HIPCHK(hipStreamSynchronize(L->stream));
     if (int rc = check_small(L)) return rc;
+    L->stats_dirty = false;
+    const StatSlot &s = L->host->stats;
     for (int i = 0; i < 3; ++i) {
         out->attempts[i] = s.attempts[i];
         out->accepts[i] = s.accepts[i];
@@ -946,7 +968,7 @@ int su3hb_sweep(su3hb_lattice *L, double beta0, double beta1, int n_hit, int n_s
     int rc = check_sweep_args(beta0, beta1, n_hit, n_sweeps);
     if (rc) return rc;
     HIPCHK(hipSetDevice(L->device));
-    if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
+    if (stats && (rc = begin_stats(L)) != SU3HB_OK) return rc;
     rc = run_sweeps(L, beta0, beta1, n_hit, n_sweeps, 0, stats != nullptr);
     if (rc) return rc;
     if (stats) return read_stats(L, stats);
@@ -959,7 +981,7 @@ int su3hb_overrelax(su3hb_lattice *L, double beta0, double beta1, int n_sweeps, 
     int rc = check_sweep_args(beta0, beta1, 1, n_sweeps);
     if (rc) return rc;
     HIPCHK(hipSetDevice(L->device));
-    if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
+    if (stats && (rc = begin_stats(L)) != SU3HB_OK) return rc;
     rc = run_sweeps(L, beta0, beta1, 0, n_sweeps, 0, stats != nullptr);  // n_hit 0: overrelaxation
     if (rc) return rc;
     if (stats) return read_stats(L, stats);
@@ -975,18 +997,16 @@ int su3hb_sweep_measure(su3hb_lattice *L, double beta0, double beta1, int n_hit,
     int rc = check_sweep_args(beta0, beta1, n_hit, n_sweeps);
     if (rc) return rc;
     HIPCHK(hipSetDevice(L->device));
-    if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
+    if (stats && (rc = begin_stats(L)) != SU3HB_OK) return rc;
     for (int done = 0; done < n_sweeps;) {
         int chunk = std::min<int>(int(kSeriesCap), n_sweeps - done);
         rc = ensure_meas(L, chunk, &chunk);
         if (rc) return rc;
-        if (!use_small(L)) HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
         rc = run_sweeps(L, beta0, beta1, n_hit, chunk, 1, stats != nullptr);
-        if (!rc) rc = finish_measure(L, beta0, beta1, chunk, L->d_series);
+        if (!rc && !use_small(L)) rc = finish_measure(L, beta0, beta1, chunk, L->host->series);
         if (rc) return rc;
-        HIPCHK(hipMemcpyAsync(series + size_t(done) * 6, L->d_series, sizeof(double) * 6 * chunk,
-                              hipMemcpyDeviceToHost, L->stream));
         HIPCHK(hipStreamSynchronize(L->stream));
+        std::memcpy(series + size_t(done) * 6, L->host->series, sizeof(double) * 6 * size_t(chunk));
         if ((rc = check_small(L)) != SU3HB_OK) return rc;
         done += chunk;
     }
@@ -1001,8 +1021,8 @@ int su3hb_plaquette(su3hb_lattice *L, double beta0, double beta1, double out[6])
     HIPCHK(hipSetDevice(L->device));
     int rc = enqueue_plaquette(L, L->stream, beta0, beta1);
     if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(out, L->d_plaq, sizeof(double) * 6, hipMemcpyDeviceToHost, L->stream));
     HIPCHK(hipStreamSynchronize(L->stream));
+    std::memcpy(out, L->host_plaq, sizeof(double) * 6);
     return check_small(L);
 }
 
@@ -1190,6 +1210,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     hipEventDestroy(e1);
     HIPCHK(hipMemcpyAsync(L->links, backup, L->links_bytes, hipMemcpyDeviceToDevice, L->stream));
     HIPCHK(launch_counter_set(L->stream, L->d_sweep, uint32_t(sweep0)));
+    HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
     HIPCHK(hipStreamSynchronize(L->stream));
     L->sweep = sweep0;
     if (rc) return rc;
@@ -1224,12 +1245,11 @@ int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, i
     std::vector<int> kinds;
     kinds.reserve(launches);
     for (int sw = 0; sw < n_sweeps; ++sw) {
-        if (measure) HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
         rc = enqueue_sweep(L, L->stream, beta0, beta1, n_hit, measure, false, &kinds, &ev);
         if (rc) return rc;
         if (!measure) continue;
         HIPCHK(hipEventRecord(L->events[ev++], L->stream));
-        rc = finish_measure(L, beta0, beta1, 1, L->d_series + size_t(sw) * 6);
+        rc = finish_measure(L, beta0, beta1, 1, L->host->series + size_t(sw) * 6);
         if (rc) return rc;
         HIPCHK(hipEventRecord(L->events[ev++], L->stream));
         kinds.push_back(1);
@@ -1253,9 +1273,7 @@ int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, i
     timing[2] = t_plq;
     timing[3] = n_plq;
     if (measure && n_sweeps > 0) {
-        HIPCHK(hipMemcpyAsync(series, L->d_series, sizeof(double) * 6 * n_sweeps, hipMemcpyDeviceToHost,
-                              L->stream));
-        HIPCHK(hipStreamSynchronize(L->stream));
+        std::memcpy(series, L->host->series, sizeof(double) * 6 * size_t(n_sweeps));
     }
     return SU3HB_OK;
 }
@@ -1315,7 +1333,7 @@ int su3hb_batch_sweep(su3hb_batch *L, int n_hit, int n_sweeps, int mode, su3hb_s
     if (rc) return rc;
     if (mode != 0 && mode != 1) return fail(SU3HB_EINVAL, "mode = %d, expected 0 or 1", mode);
     HIPCHK(hipSetDevice(L->device));
-    if (stats) HIPCHK(launch_stats_zero(L->stream, L->d_stats));
+    if (stats && (rc = begin_stats(L)) != SU3HB_OK) return rc;
     if (mode == 0) {
         rc = run_sweeps(L, 0.0, 0.0, n_hit, n_sweeps, 0, stats != nullptr);
         if (rc) return rc;
@@ -1358,8 +1376,8 @@ int su3hb_batch_plaquette(su3hb_batch *L, double *out, size_t n)
     HIPCHK(hipSetDevice(L->device));
     int rc = enqueue_plaquette(L, L->stream, 0.0, 0.0);
     if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(out, L->d_plaq, sizeof(double) * n, hipMemcpyDeviceToHost, L->stream));
     HIPCHK(hipStreamSynchronize(L->stream));
+    std::memcpy(out, L->host_plaq, sizeof(double) * n);
     return check_small(L);
 }
 
@@ -1466,10 +1484,10 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     // set-up: no memset nodes (kernels clear what must start at zero)
     HIPCHK(launch_rep_set(st, rep, d_rep));
     HIPCHK(launch_counter_set(st, d_sweep, uint32_t(sweep0)));
+    HIPCHK(launch_measure_begin(st, d_sweep));
     // measured sweeps in runs whose partial sums fit the scratch
     const int run = series ? int(std::min<size_t>(size_t(n_sweeps), kScratchMeasDoubles / meas_doubles)) : n_sweeps;
     for (int sw = 0; sw < n_sweeps; ++sw) {
-        if (series && sw % run == 0) HIPCHK(launch_measure_begin(st, d_sweep));
         for (int par = 0; par < 2; ++par)
             for (int mu = 0; mu < p->nd; ++mu) {
                 a.parity = par;
@@ -1480,7 +1498,7 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
         const int done = sw % run + 1;
         if (series && (done == run || sw + 1 == n_sweeps))
             HIPCHK(launch_measure_finalize(st, d_meas, done, p->nd, blocks, nc, double(rep.V), int(rep.nlat),
-                                           beta0, beta1, series + size_t(sw + 1 - done) * 6));
+                                           beta0, beta1, series + size_t(sw + 1 - done) * 6, d_sweep));
     }
     return SU3HB_OK;
 }

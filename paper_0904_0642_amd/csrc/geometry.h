@@ -20,6 +20,25 @@ __device__ __forceinline__ uint32_t first_block(const RepDesc &r, int kind)
                                        : r.upd_block0;
 }
 
+// The six numbers of a plaquette measurement from the sums over the planes
+// [spacelike, timelike] x class (measure_finalize_kernel).
+__device__ __forceinline__ void plaquette_row(const double v[6], int D, double V, int nlat, double beta0, double beta1,
+                                              double *out)
+{
+    const double nV = double(nlat) * V;
+    const double nspace = nV * (D - 1) * (D - 2) / 2.0, ntime = nV * (D - 1);
+    const double nlayer = V * D * (D - 1) / 2.0;
+    const double nan = __builtin_nan("");
+    const double space = v[0] + v[1] + v[2], time = v[3] + v[4] + v[5];
+    const double t0 = v[0] + v[3], t1 = v[1] + v[4], t2 = v[2] + v[5];
+    out[0] = (space + time) / (nspace + ntime);
+    out[1] = nspace > 0 ? space / nspace : nan;
+    out[2] = time / ntime;
+    out[3] = (t0 + t1) / nlayer;
+    out[4] = nlat == 2 ? t2 / nlayer : nan;
+    out[5] = beta0 * t0 + beta1 * (t1 + t2);
+}
+
 // Find the replica owning logical block lb: largest r with first[r] <= lb.
 // The block index and the table are uniform, so this runs on scalar units.
 __device__ __forceinline__ int find_replica(const RepDesc *__restrict__ reps, int nrep, uint32_t lb, int kind)

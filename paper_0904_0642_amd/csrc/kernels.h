@@ -16,10 +16,8 @@ hipError_t launch_update(int D, int prec, int waves, dim3 grid, dim3 block, hipS
 // (split.h); a.total_blocks counts blocks of kSplitLinks links
 hipError_t launch_update_split(int D, int prec, hipStream_t st, const UpdateArgs &a);
 
-// whole sweeps of a small lattice or batch in one launch, after
-// launch_small_begin for the same number of sweeps
+// whole sweeps of a small lattice or batch in one launch
 hipError_t launch_update_small(int D, int prec, hipStream_t st, const SmallArgs &s);
-hipError_t launch_small_begin(hipStream_t st, uint32_t *sweep, uint32_t n_sweeps, uint32_t *work);
 
 // LDS one block of such a launch needs (static + dynamic) and the device's
 // per-block limit; the caller refuses launches that would not fit
@@ -37,9 +35,10 @@ hipError_t launch_plaquette_finalize(hipStream_t st, const RepDesc *reps, int nr
 
 // fused measurement of n sweeps: sums the per-block plaquette class partials
 // (nc = 1 for one layer, 3 for two) that the parity-1 update slices of each
-// sweep wrote, normalises like the plaquette path, into series (6 per sweep)
+// sweep wrote, normalises like the plaquette path, into series (6 per sweep),
+// and sets the counter's word 2 back (kSweepWords)
 hipError_t launch_measure_finalize(hipStream_t st, const double *meas, int n, int D, uint32_t nblocks, int nc,
-                                   double V, int nlat, double beta0, double beta1, double *series);
+                                   double V, int nlat, double beta0, double beta1, double *series, uint32_t *sweep);
 
 // start configuration of one replica: mode 1 ordered, 2 Haar
 hipError_t launch_start(int D, int prec, hipStream_t st, void *links, const RepDesc *reps, int r,
@@ -60,10 +59,11 @@ hipError_t launch_rep_set(hipStream_t st, const RepDesc &r, RepDesc *dst);
 
 // statistics slots and counters
 hipError_t launch_stats_zero(hipStream_t st, StatSlot *slots);
-hipError_t launch_stats_reduce(hipStream_t st, const StatSlot *slots, StatSlot *out);
+// sums the slots and empties them
+hipError_t launch_stats_reduce(hipStream_t st, StatSlot *slots, StatSlot *out);
 hipError_t launch_counter_add(hipStream_t st, uint32_t *ctr, uint32_t add);
 hipError_t launch_counter_set(hipStream_t st, uint32_t *ctr, uint32_t value);
-// the counter's word 2 from its word 0: measured sweeps begin (kSweepWords)
+// the counter's word 2 to 0: partial sums that wait are dropped (kSweepWords)
 hipError_t launch_measure_begin(hipStream_t st, uint32_t *sweep);
 hipError_t launch_u32_zero(hipStream_t st, uint32_t *p, int n);
 hipError_t launch_u64_zero(hipStream_t st, unsigned long long *p, int n);

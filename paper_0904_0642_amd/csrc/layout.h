@@ -95,9 +95,10 @@ constexpr uint32_t kBarrierSpinLimit = 1u << 22;
 // launch of its own: a launch of one wave costs 4.4 us inside a replayed
 // graph, and so did adding up each sweep's plaquettes (5.7 us), now one launch
 // for all sweeps of a call (4^4 FP64-18, 20 measured sweeps: 2.46 -> 2.13 ms;
-// 16^4, 4 sweeps: 0.70 -> 0.64 ms).  Word 2 is the index of the first sweep of a measured
-// run: sweep i writes its partial sums at place i - word 2 of `meas`.
-constexpr int kSweepWords = 3;
+// 16^4, 4 sweeps: 0.70 -> 0.64 ms).  Words 2 and 3 count the measured sweeps whose
+// partial sums wait in `meas` in the same way (word 3 is read by the measured
+// slices); adding them up sets word 2 back to 0.
+constexpr int kSweepWords = 4;
 
 // Launches that share a link's update between lanes and waves (split.h): links
 // of a block; blocks ("groups") of a slice up to which the library takes them
@@ -148,20 +149,25 @@ struct UpdateArgs {
 };
 
 // Whole sweeps in one launch (small lattices): the next ticket, the XCD that
-// works and, for every group of 16 links, the slices it has done; cleared
+// works (plus 1) and, for every group of 16 links, the slices it has done; cleared
 // before the launch.  Up to 64 groups an XCD gives each its block (two per
 // compute unit in FP64); with two rounds of blocks a slice takes longer than
 // launched by itself (2048 links, FP64-18: 9.9 us against 6.9 us).
 constexpr uint32_t kSmallGroups = 64;
 constexpr uint32_t kSmallTicket = 0, kSmallXcd = 32, kSmallDone = 64, kSmallWords = kSmallDone + kSmallGroups;
-constexpr uint32_t kSmallNoXcd = 0xFFFFFFFFu;
+constexpr uint32_t kSmallQueues = 64;             // queues cleared together; each launch takes the next one
 constexpr uint32_t kSmallSpinLimit = 1u << 24;
 
 struct SmallArgs {
     UpdateArgs u;                // total_blocks: groups of a slice
     uint32_t items;              // 2 D n_sweeps total_blocks, below 2^31
     DivMagic per_slice;          // division by total_blocks
-    uint32_t *work;              // kSmallWords words
+    uint32_t sweep0;             // index of the first sweep
+    uint32_t sweeps;             // sweeps of the launch
+    double V;                    // sites per layer
+    int nlat;
+    double *series;              // measured sweeps: 6 numbers each, in host memory
+    uint32_t *work;              // kSmallWords words, zero
     uint32_t *failed;            // host memory: set to 1 by a wait past its limit
 };
 

@@ -23,18 +23,21 @@ __device__ __forceinline__ bool inv_norm(double k2, double &ik)
     return true;
 }
 
-// The place of this sweep's partial sums (parity-1 slices).
+// The partial sums of block b in a measured slice of the place-th measured
+// sweep.
 template <int D, int NC>
-__device__ __forceinline__ double *meas_of_sweep(const UpdateArgs &a, uint32_t sweep)
+__device__ __forceinline__ double *meas_of_block(const UpdateArgs &a, uint32_t place, uint32_t b)
 {
-    return a.meas + size_t(sweep - a.sweep[2]) * (size_t(D) * a.total_blocks * NC);
+    return a.meas + ((size_t(place) * D + uint32_t(a.mu)) * a.total_blocks + b) * NC;
 }
 
 // The sweep counter's step at the end of each parity (one thread per launch;
 // kSweepWords in layout.h).
 __device__ __forceinline__ void advance_sweep(const UpdateArgs &a, int D, uint32_t sweep)
 {
-    if (a.mu == D - 1 && blockIdx.x == 0 && threadIdx.x == 0) a.sweep[1 - a.parity] = sweep + uint32_t(a.parity);
+    if (a.mu != D - 1 || blockIdx.x != 0 || threadIdx.x != 0) return;
+    a.sweep[1 - a.parity] = sweep + uint32_t(a.parity);
+    if (a.meas != nullptr) a.sweep[3 - a.parity] = a.sweep[2 + a.parity] + uint32_t(a.parity);
 }
 
 // Between a wave's LDS writes and its lanes' reads of them: the wave's LDS

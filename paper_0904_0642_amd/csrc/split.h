@@ -581,9 +581,9 @@ __device__ __forceinline__ void split_update(const UpdateArgs &a, const RepDesc 
 }
 
 // A wave's counters into a slot of the statistics, its measurement into the
-// partial sums of its group.
+// partial sums of its group, of the place-th measured sweep.
 template <int D, int NC>
-__device__ __forceinline__ void split_flush(const UpdateArgs &a, uint32_t group, uint32_t sweep, SplitSums<NC> &v)
+__device__ __forceinline__ void split_flush(const UpdateArgs &a, uint32_t group, uint32_t place, SplitSums<NC> &v)
 {
     const uint32_t lane = threadIdx.x & 63u;
     if (a.meas != nullptr && a.parity == 1) {
@@ -592,7 +592,7 @@ __device__ __forceinline__ void split_flush(const UpdateArgs &a, uint32_t group,
 #pragma unroll
             for (int k = 0; k < NC; ++k) v.plaq[k] += __shfl_xor(v.plaq[k], off);
         if (lane == 0) {
-            double *m = meas_of_sweep<D, NC>(a, sweep) + (size_t(a.mu) * a.total_blocks + group) * NC;
+            double *m = meas_of_block<D, NC>(a, place, group);
 #pragma unroll
             for (int k = 0; k < NC; ++k) m[k] = v.plaq[k];
         }

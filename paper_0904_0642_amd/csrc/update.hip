@@ -304,8 +304,8 @@ __device__ __forceinline__ void update_link(const UpdateArgs &a, const RepDesc &
 // NC plaquette class sums (plain stores, one group per (direction, block),
 // added up later in a fixed order).
 template <int D, int NC>
-__device__ __forceinline__ void flush_stats(const UpdateArgs &a, uint32_t lb, uint32_t sweep, int att[3], int acc[3],
-                                            int upd, double dtrace, double *plaq)
+__device__ __forceinline__ void flush_stats(const UpdateArgs &a, uint32_t lb, int att[3], int acc[3], int upd,
+                                            double dtrace, double *plaq)
 {
     const bool measured = a.meas != nullptr && a.parity == 1;
     if (a.stats == nullptr && !measured) return;
@@ -349,7 +349,7 @@ __device__ __forceinline__ void flush_stats(const UpdateArgs &a, uint32_t lb, ui
             unsafeAtomicAdd(&sl->dtrace, dtrace);
         }
         if (measured && lb < a.total_blocks) {
-            double *m = meas_of_sweep<D, NC>(a, sweep) + (size_t(a.mu) * a.total_blocks + lb) * NC;
+            double *m = meas_of_block<D, NC>(a, a.sweep[3], lb);
 #pragma unroll
             for (int c = 0; c < NC; ++c) m[c] = plaq[c];
         }
@@ -433,7 +433,7 @@ __device__ __forceinline__ void process_block(const UpdateArgs &a, uint32_t lb, 
 #pragma unroll
     for (int c = 0; c < NC; ++c) plaq[c] = 0.0;
     block_links<D, PREC, NC>(a, lb, sweep, att, acc, upd, dtrace, plaq, lt_override);
-    flush_stats<D, NC>(a, lb, sweep, att, acc, upd, dtrace, plaq);
+    flush_stats<D, NC>(a, lb, att, acc, upd, dtrace, plaq);
 }
 
 // Logical block of hardware block b.  Hardware blocks are dealt round-robin
@@ -696,7 +696,7 @@ __global__ void __launch_bounds__(THREADS, persistent_waves(PREC)) update_persis
                     const uint32_t lb = first + (back ? n - 1u - j : j) * step;
                     block_links<D, PREC, 1>(b, lb, sweep0 + uint32_t(sw), att, acc, upd, dtrace, plaq);
                 }
-                flush_stats<D, 1>(b, blockIdx.x, sweep0 + uint32_t(sw), att, acc, upd, dtrace, plaq);
+                flush_stats<D, 1>(b, blockIdx.x, att, acc, upd, dtrace, plaq);
                 if (!xcd_barrier(a.barrier, gen++, x, members, nxcd)) return;
             }
         }

@@ -63,8 +63,49 @@ __global__ void __launch_bounds__(256, 2) update_split_kernel(UpdateArgs a)
     const SplitColumn<PREC, NC> col = split_sum<D, PREC, NC>(a, rep, lds);
     SplitSums<NC> sums;
     split_update<D, PREC, NC>(a, rep, site, sweep, col, U, draw, uptr, table, sums);
-    split_flush<D, NC>(a, group, sweep, sums);
+    split_flush<D, NC>(a, group, a.meas != nullptr ? a.sweep[3] : 0u, sums);
     advance_sweep(a, D, sweep);
+}
+
+// Wait until every group has done n slices; false past the limit.
+__device__ __forceinline__ bool small_wait(const SmallArgs &s, uint32_t n, uint32_t lane)
+{
+    uint32_t spins = 0;
+    while (__any(lane < s.u.total_blocks &&
+                 __hip_atomic_load(s.work + kSmallDone + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)) {
+        if (++spins > kSmallSpinLimit) {
+            if (lane == 0) *s.failed = 1u;
+            return false;
+        }
+        __builtin_amdgcn_s_sleep(2);
+    }
+    return true;
+}
+
+// The end of a launch of whole sweeps: the sweep counter, and the plaquettes
+// of measured sweeps, a sweep per wave at a time.  The sums are those of
+// measure_finalize_kernel, whose first wave holds all groups.
+template <int D, int NC>
+__device__ __forceinline__ void small_finish(const SmallArgs &s, uint32_t wave, uint32_t lane)
+{
+    if (!small_wait(s, 2u * D * s.sweeps, lane)) return;
+    if (wave == 0 && lane == 0) s.u.sweep[0] = s.sweep0 + s.sweeps;
+    if (s.u.meas == nullptr) return;
+    for (uint32_t sw = wave; sw < s.sweeps; sw += 4u) {
+        double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        UpdateArgs a = s.u;
+        for (a.mu = 1; a.mu < D; ++a.mu)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                if (lane < a.total_blocks)
+                    v[(a.mu == D - 1 ? 3 : 0) + c] += __hip_atomic_load(meas_of_block<D, NC>(a, sw, lane) + c,
+                                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int i = 0; i < 6; ++i) v[i] += __shfl_xor(v[i], off);
+        if (lane == 0) plaquette_row(v, D, s.V, s.nlat, a.beta0, a.beta1, s.series + size_t(sw) * 6);
+    }
 }
 
 // Whole sweeps of a lattice so small that even its slices' launches cost more
@@ -106,10 +147,10 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
     };
     if (threadIdx.x == 0) {
         const uint32_t x = xcc_id();
-        uint32_t old = kSmallNoXcd;
-        __hip_atomic_compare_exchange_strong(s.work + kSmallXcd, &old, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+        uint32_t old = 0;
+        __hip_atomic_compare_exchange_strong(s.work + kSmallXcd, &old, x + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
-        s_mine = old == kSmallNoXcd || old == x;
+        s_mine = old == 0u || old == x + 1u;
         if (s_mine) s_ticket = take();
         s_round = 1;
         s_go = 0;
@@ -119,17 +160,21 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
     if (!s_mine) return;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t sweep0 = s.u.sweep[2];
     SplitLds<D, PREC> lds(s_lds);
     for (uint32_t round = 1;; ++round) {
         uint32_t spins = 0;
         while (__hip_atomic_load(&s_round, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != round)
             if (++spins > kSmallSpinLimit) return;
         const uint32_t t = __builtin_amdgcn_readfirstlane(s_ticket);
-        if (t >= s.items) return;
+        if (t >= s.items) {
+            // one block, with the first ticket past the end, adds up the
+            // plaquettes and steps the sweep counter
+            if (t == s.items) small_finish<D, NC>(s, wave, lane);
+            return;
+        }
         const uint32_t n = div_by(t, s.per_slice), group = t - n * s.u.total_blocks;
         UpdateArgs a = s.u;
-        const uint32_t sw = n / (2u * D), sl = n - sw * (2u * D), sweep = sweep0 + sw;
+        const uint32_t sw = n / (2u * D), sl = n - sw * (2u * D), sweep = s.sweep0 + sw;
         a.parity = sl >= uint32_t(D) ? 1 : 0;
         a.mu = int(sl) - a.parity * D;
         const RepDesc &rep = a.reps[a.nrep == 1 ? 0 : find_replica(a.reps, a.nrep, group, kSplitBlocks)];
@@ -148,7 +193,7 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
             __syncthreads();  // and read
             SplitSums<NC> sums;
             split_update<D, PREC, NC>(a, rep, site, sweep, col, U, draw, uptr, table, sums);
-            split_flush<D, NC>(a, group, sweep, sums);
+            split_flush<D, NC>(a, group, sw, sums);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane == 0)
                 __hip_atomic_store(s.work + kSmallDone + group, n + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -175,15 +220,7 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
         // (reads that pass the caches by: more of them would slow the links')
         // and tells wave 2
         if (wave == 1) {
-            while (__any(lane < s.u.total_blocks &&
-                         __hip_atomic_load(s.work + kSmallDone + lane, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT) < n)) {
-                if (++spins > kSmallSpinLimit) {
-                    if (lane == 0) *s.failed = 1u;
-                    return;
-                }
-                __builtin_amdgcn_s_sleep(2);
-            }
+            if (!small_wait(s, n, lane)) return;
             if (lane == 0) __hip_atomic_store(&s_go, round, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
             while (__hip_atomic_load(&s_go, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != round)

@@ -106,6 +106,16 @@ def test_forms_alternate_on_one_lattice():
     assert a.get_state() == b.get_state() == (2, 21)
 
 
+def test_many_launches_take_queue_after_queue():
+    # more launches of whole sweeps than there are queues between two clearings
+    a, b = (su3hb.Lattice([4, 4, 2, 4], seed=5) for _ in range(2))
+    parts = [a.sweep_measure(5.7, n_sweeps=1) if k % 3 else a.sweep(5.7, n_sweeps=1) for k in range(150)]
+    b.sweep_measure(5.7, n_sweeps=150)
+    assert np.array_equal(a.get_links(), b.get_links()) and a.get_state() == b.get_state()
+    assert np.array_equal(a.sweep_measure(5.7, n_sweeps=2), b.sweep_measure(5.7, n_sweeps=2), equal_nan=True)
+    assert all(p is None or p.shape == (1, 6) for p in parts)
+
+
 def test_lattices_on_two_streams():
     # two lattices whose launches may run side by side keep their queues apart
     import torch
