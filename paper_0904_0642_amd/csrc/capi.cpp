@@ -1,7 +1,7 @@
 // capi.cpp -- the extern "C" boundary of libsu3hb.so (declared in
 // include/su3hb.h): argument checks, device memory, the sweep driver
-// (parity outer, direction inner; one launch per slice, replayed from a
-// captured HIP graph), measurement, canonical get/set, autotuning and batches.
+// (parity outer, direction inner; one launch per slice), measurement,
+// canonical get/set, autotuning and batches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,19 +52,6 @@ constexpr uint32_t kSeriesCap = 4096;
 constexpr size_t kStageBytes = size_t(256) << 20;
 constexpr size_t kMeasBytes = size_t(64) << 20;  // partial sums kept before they are added up
 
-// A captured sweep, keyed by its couplings, kind (n_hit; 0 = overrelaxation),
-// measurement and whether it keeps counters.  A few are kept so that heatbath and overrelaxation sweeps
-// can alternate without capturing again.
-struct GraphCache {
-    bool valid = false;
-    double b0 = 0, b1 = 0;
-    int nhit = 0, measure = 0, counters = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    uint64_t used = 0;
-};
-constexpr int kGraphSlots = 4;
-
 }  // namespace
 
 struct su3hb_lattice {
@@ -78,7 +65,6 @@ struct su3hb_lattice {
     size_t links_bytes = 0;
     bool owns_links = false;
     hipStream_t stream = nullptr;
-    hipStream_t cap = nullptr;
     uint32_t *d_sweep = nullptr;
     uint64_t sweep = 0;
     uint64_t seed = 0;
@@ -105,9 +91,6 @@ struct su3hb_lattice {
     uint32_t *d_work = nullptr;   // queues of launches that hold whole sweeps
     uint32_t small_launches = 0;  // such launches so far
     uint32_t upd_blocks = 0, plq_blocks = 0, pers_blocks = 0;
-    bool use_graph = true;
-    GraphCache graphs[kGraphSlots];
-    uint64_t graph_tick = 0;
     std::vector<hipEvent_t> events;
     int num_cus = 0;
 };
@@ -127,18 +110,6 @@ struct Shape {
     bool automatic;  // left to use_split
 };
 std::map<std::string, Shape> g_tune_cache;
-
-void drop_slot(GraphCache &g)
-{
-    if (g.exec) hipGraphExecDestroy(g.exec);
-    if (g.graph) hipGraphDestroy(g.graph);
-    g = GraphCache{};
-}
-
-void drop_graph(su3hb_lattice *L)
-{
-    for (auto &g : L->graphs) drop_slot(g);
-}
 
 // The shape of lattices and batches for which none is set: where it applies,
 // XCD slabs with the waves of a block along x_{D-2}, else XCD runs, and
@@ -251,7 +222,6 @@ int alloc_common(su3hb_lattice *L)
 {
     HIPCHK(hipGetDevice(&L->device));
     HIPCHK(hipDeviceGetAttribute(&L->num_cus, hipDeviceAttributeMultiprocessorCount, L->device));
-    HIPCHK(hipStreamCreateWithFlags(&L->cap, hipStreamNonBlocking));
     HIPCHK(hipHostMalloc(&L->host, sizeof(*L->host) + sizeof(double) * 6 * L->reps.size(), 0));
     L->host->failed = 0;
     L->host_plaq = reinterpret_cast<double *>(L->host + 1);
@@ -311,14 +281,12 @@ void destroy(su3hb_lattice *L)
     if (!L) return;
     hipSetDevice(L->device);
     hipStreamSynchronize(L->stream);   // also the null stream: nothing may still run on this memory
-    drop_graph(L);
     for (auto e : L->events) hipEventDestroy(e);
     if (L->owns_links && L->links) hipFree(L->links);
     hipFree(L->d_tables);
     hipFree(L->d_meas);
     hipFree(L->d_stage);
     hipHostFree(L->host);
-    if (L->cap) hipStreamDestroy(L->cap);
     delete L;
 }
 
@@ -500,9 +468,8 @@ int ensure_meas(su3hb_lattice *L, int n, int *slots)
     // at least 16 sweeps and twice the last size: calls of growing length do
     // not allocate each time
     const size_t need = one * std::min(most, std::max({size_t(*slots), size_t(16), 2 * L->meas_cap / one}));
-    // captured sweeps hold the old buffer's address
+    // sweeps that run may still write the old buffer
     HIPCHK(hipStreamSynchronize(L->stream));
-    drop_graph(L);
     hipFree(L->d_meas);
     L->d_meas = nullptr;
     L->meas_cap = 0;
@@ -512,32 +479,45 @@ int ensure_meas(su3hb_lattice *L, int n, int *slots)
     return SU3HB_OK;
 }
 
-// One sweep: parity 0 then 1, directions 0..D-1 inside; the last slice steps
-// the counter.  measure != 0 (single lattices): the parity-1 slices leave the
-// partial sums of the plaquettes (finish_measure adds them up).  `timed`
-// (optional) records an event pair around every update launch.
-int enqueue_sweep(su3hb_lattice *L, hipStream_t st, double b0, double b1, int nhit, int measure, bool counters,
-                  std::vector<int> *timed = nullptr, size_t *ev = nullptr)
+// The arguments of a sweep's launches, checked against the device's LDS.
+int sweep_args(const su3hb_lattice *L, double b0, double b1, int nhit, int measure, bool counters, UpdateArgs *out)
 {
     UpdateArgs a = update_args(L, b0, b1, nhit, counters);
     if (measure) {
         a.meas = L->d_meas;
         a.meas_classes = meas_classes(L);
     }
-    const bool split = use_split(L);
-    if (split) a.total_blocks = L->split_groups;
-    const dim3 grid = update_grid(L), block(L->block);
-    if (!split) {
+    if (use_split(L)) {
+        a.total_blocks = L->split_groups;
+    } else {
         // the largest LDS request of the sweep (a measured parity-1 slice)
         // must fit one block's share of the compute unit
         UpdateArgs m = a;
         m.parity = 1;
         size_t need = 0, limit = 0;
-        HIPCHK(update_lds(L->nd, L->prec, L->waves, block, m, &need, &limit));
+        HIPCHK(update_lds(L->nd, L->prec, L->waves, dim3(L->block), m, &need, &limit));
         if (limit == 0 || need > limit)
             return fail(SU3HB_EUNSUPPORTED, "update launch needs %zu bytes of LDS per block, the device allows %zu",
                         need, limit);
     }
+    *out = a;
+    return SU3HB_OK;
+}
+
+// One sweep by sweep_args: parity 0 then 1, directions 0..D-1 inside; the last
+// slice steps the counter.  Measured (single lattices): the parity-1 slices
+// leave the partial sums of the plaquettes (finish_measure adds them up).
+// `timed` (optional) records an event pair around every update launch.  Plain
+// launches: a replayed graph of the same slices takes 0.2 to 0.6 us a slice
+// longer (16^4 FP64-18 16.8 against 16.1 us, 30x22x18 FP32-12 7.6 against 7.2 us),
+// and capturing it the first call 75 us; the host enqueues a slice in 3.6 us.
+int enqueue_sweep(su3hb_lattice *L, const UpdateArgs &first, std::vector<int> *timed = nullptr,
+                  size_t *ev = nullptr)
+{
+    UpdateArgs a = first;
+    const bool split = use_split(L);
+    const dim3 grid = update_grid(L), block(L->block);
+    hipStream_t st = L->stream;
     for (int p = 0; p < 2; ++p)
         for (int mu = 0; mu < L->nd; ++mu) {
             a.parity = p;
@@ -560,51 +540,6 @@ int finish_measure(su3hb_lattice *L, double b0, double b1, int n, double *series
 {
     HIPCHK(launch_measure_finalize(L->stream, L->d_meas, n, L->nd, meas_blocks(L), meas_classes(L),
                                    double(L->reps[0].V), int(L->reps[0].nlat), b0, b1, series, L->d_sweep));
-    return SU3HB_OK;
-}
-
-int get_graph(su3hb_lattice *L, double b0, double b1, int nhit, int measure, bool counters, hipGraphExec_t *out)
-{
-    GraphCache *slot = nullptr;
-    for (auto &g : L->graphs)
-        if (g.valid && g.b0 == b0 && g.b1 == b1 && g.nhit == nhit && g.measure == measure &&
-            g.counters == int(counters)) {
-            g.used = ++L->graph_tick;
-            *out = g.exec;
-            return SU3HB_OK;
-        }
-    // an empty slot, else the least recently used one
-    for (auto &g : L->graphs)
-        if (!slot || !g.valid || (slot->valid && g.used < slot->used)) {
-            slot = &g;
-            if (!g.valid) break;
-        }
-    drop_slot(*slot);
-    HIPCHK(hipStreamBeginCapture(L->cap, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_sweep(L, L->cap, b0, b1, nhit, measure, counters);
-    hipGraph_t graph = nullptr;
-    hipError_t e = hipStreamEndCapture(L->cap, &graph);
-    if (rc) {
-        if (graph) hipGraphDestroy(graph);
-        return rc;
-    }
-    if (e != hipSuccess) return fail(SU3HB_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-    hipGraphExec_t exec = nullptr;
-    e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) {
-        hipGraphDestroy(graph);
-        return fail(SU3HB_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-    }
-    slot->valid = true;
-    slot->b0 = b0;
-    slot->b1 = b1;
-    slot->nhit = nhit;
-    slot->measure = measure;
-    slot->counters = counters;
-    slot->graph = graph;
-    slot->exec = exec;
-    slot->used = ++L->graph_tick;
-    *out = exec;
     return SU3HB_OK;
 }
 
@@ -664,18 +599,19 @@ int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int meas
 {
     if (n <= 0) return SU3HB_OK;
     if (int rc = check_sweep_room(L, n)) return rc;
+    // a captured call could be replayed, with sweeps that this handle would not
+    // count (su3hb_sweep_measure_static is the call for that); the null stream
+    // cannot be captured
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (L->stream) HIPCHK(hipStreamIsCapturing(L->stream, &capture));
+    if (capture != hipStreamCaptureStatusNone) return fail(SU3HB_EHIP, "the stream is being captured");
     if (use_small(L)) {
         if (int rc = run_small(L, b0, b1, nhit, n, measure, counters)) return rc;
-    } else if (L->use_graph) {
-        hipGraphExec_t exec = nullptr;
-        int rc = get_graph(L, b0, b1, nhit, measure, counters, &exec);
-        if (rc) return rc;
-        for (int i = 0; i < n; ++i) HIPCHK(hipGraphLaunch(exec, L->stream));
     } else {
-        for (int i = 0; i < n; ++i) {
-            int rc = enqueue_sweep(L, L->stream, b0, b1, nhit, measure, counters);
-            if (rc) return rc;
-        }
+        UpdateArgs a;
+        if (int rc = sweep_args(L, b0, b1, nhit, measure, counters, &a)) return rc;
+        for (int i = 0; i < n; ++i)
+            if (int rc = enqueue_sweep(L, a)) return rc;
     }
     L->sweep += uint64_t(n);
     return SU3HB_OK;
@@ -806,7 +742,6 @@ int apply_launch(su3hb_lattice *L, int block, int order, int waves)
     if (waves != 2 && !(waves == 3 && L->nd == 4) && !(waves == 4 && L->nd == 4 && is_fp32(L->prec)))
         return fail(SU3HB_EINVAL, "waves = %d: 2, or 3 for D = 4, or 4 for D = 4 with FP32 links", waves);
     HIPCHK(hipStreamSynchronize(L->stream));
-    drop_graph(L);
     const bool old_set = L->shape_set;
     const int old_block = L->block, old_order = L->order, old_waves = L->waves;
     L->block = block;
@@ -1141,8 +1076,6 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     // slow moment of the machine does not decide the choice
     std::vector<float> per(cands.size(), 1e30f);
     size_t best_i = 0;
-    const bool graph = L->use_graph;
-    L->use_graph = false;
     int rc = SU3HB_OK;
     // time candidate i: its launch, a warm-up sweep, then timed batches of
     // at least min_reps sweeps, doubling until a batch takes target_ms (at
@@ -1157,9 +1090,11 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
         if (r) return r;
         int slots = 0;
         if (meas && (r = ensure_meas(L, 1, &slots)) != SU3HB_OK) return r;
+        UpdateArgs a;
+        if ((r = sweep_args(L, b, b, 8, meas, false, &a)) != SU3HB_OK) return r;
         auto one_sweep = [&]() -> int {
             if (meas && hipSuccess != launch_measure_begin(L->stream, L->d_sweep)) return fail(SU3HB_EHIP, "measure");
-            return enqueue_sweep(L, L->stream, b, b, 8, meas, false);
+            return enqueue_sweep(L, a);
         };
         if ((r = one_sweep()) != SU3HB_OK) return r;  // warm-up
         int reps = min_reps;
@@ -1205,7 +1140,6 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
             if (fin[k] < fin[bk]) bk = k;
         best_i = rank[bk];
     }
-    L->use_graph = graph;
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     HIPCHK(hipMemcpyAsync(L->links, backup, L->links_bytes, hipMemcpyDeviceToDevice, L->stream));
@@ -1244,8 +1178,11 @@ int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, i
     size_t ev = 0;
     std::vector<int> kinds;
     kinds.reserve(launches);
+    UpdateArgs a;
+    rc = sweep_args(L, beta0, beta1, n_hit, measure, false, &a);
+    if (rc) return rc;
     for (int sw = 0; sw < n_sweeps; ++sw) {
-        rc = enqueue_sweep(L, L->stream, beta0, beta1, n_hit, measure, false, &kinds, &ev);
+        rc = enqueue_sweep(L, a, &kinds, &ev);
         if (rc) return rc;
         if (!measure) continue;
         HIPCHK(hipEventRecord(L->events[ev++], L->stream));

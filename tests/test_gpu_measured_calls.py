@@ -35,3 +35,28 @@ def test_calls_of_any_length_give_one_chain(ext, nlat, mask, prec):
     # counters of a call hold that call only
     a.sweep(5.6, 6.0, n_sweeps=2)
     assert a.sweep(5.6, 6.0, n_sweeps=3, stats=True)["link_updates"] == 3 * a.n_links
+
+
+@pytest.mark.parametrize("ext", [[4, 4], [12, 8, 8, 8]])
+def test_sweeps_are_refused_while_the_stream_is_captured(ext):
+    # a replayed call would leave the handle's sweep index behind; the call for
+    # captured sweeps is su3hb_sweep_measure_static
+    import torch
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        g = su3hb.Lattice(ext, seed=4)
+        g.sweep(5.5, n_sweeps=1)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        x = torch.zeros(4, device="cuda")
+        graph.capture_begin()
+        x.add_(1.0)
+        with pytest.raises(su3hb.SU3HBError) as ei:
+            g.sweep(5.5, n_sweeps=1)
+        graph.capture_end()
+        assert ei.value.code == su3hb.EHIP and g.get_state() == (4, 1)
+        g.sweep(5.5, n_sweeps=1)
+        assert g.get_state() == (4, 2)
+    b = su3hb.Lattice(ext, seed=4)
+    b.sweep(5.5, n_sweeps=2)
+    assert np.array_equal(g.get_links(), b.get_links())
