@@ -115,6 +115,27 @@ __global__ void __launch_bounds__(256) plaquette_kernel(PlaqArgs a)
 // over the planes stay loops: unrolled, every plane's loads are hoisted.  Per
 // plane of the lattice (plaquette_kernel) every link crossed the memory side
 // D - 1 times: 32^4 FP64-12 330 -> 160 us.
+// Strips: from four dimensions on the tiles go kPlaqStrip steps of x_{D-2} at
+// a time along the whole of x_{D-1}, where such a strip's row is whole tiles.
+// Lexicographically, the links at x + e_{D-1} lay a whole x_{D-1} layer ahead
+// (32^4 FP64-18: 19 MB) and an XCD's L2 (4 MB) no longer had them.  Measured at
+// 32^4 and 64^3 x 32, lexicographic -> strips, whole calls: FP64-18 330 -> 303 and
+// 2700 -> 2542 us, FP64-12 186 -> 180 and 1449 -> 1343 us, FP32-18 186 -> 133 and
+// 1519 -> 1010 us, FP32-12 118 -> 118 and 910 -> 860 us.  Strips of two and eight
+// steps are slower or equal; in three dimensions, where whole layers stay in
+// L2, the divisions cost more than they give (64^3 FP64-18 45 -> 51 us).
+constexpr uint32_t kPlaqStrip = 4;
+
+template <int D>
+__device__ __forceinline__ uint32_t strip_tile(const RepDesc &rep, uint32_t t)
+{
+    const uint32_t sites = kPlaqStrip * rep.stride[D - 2];
+    if (sites % (2u * kTile) || uint32_t(rep.n[D - 2]) % kPlaqStrip) return t;
+    const uint32_t row = sites / (2u * kTile), last = uint32_t(rep.n[D - 1]);
+    const uint32_t strip = t / (row * last), rem = t - strip * (row * last), x = rem / row;
+    return (x * (uint32_t(rep.n[D - 2]) / kPlaqStrip) + strip) * row + (rem - x * row);
+}
+
 template <int D, int PREC>
 __global__ void __launch_bounds__(256, 2) plaquette_site_kernel(PlaqArgs a)
 {
@@ -135,7 +156,9 @@ __global__ void __launch_bounds__(256, 2) plaquette_site_kernel(PlaqArgs a)
         if (w >= waves) break;
         const uint32_t layer = w >= 2u * tiles ? 1u : 0u, wl = w - layer * 2u * tiles;
         const int p = int(wl & 1u), q = 1 - p;
-        const uint32_t h = (wl >> 1) * kTile + (threadIdx.x & 63u);
+        uint32_t tile = __builtin_amdgcn_readfirstlane(wl >> 1);
+        if constexpr (D >= 4) tile = strip_tile<D>(rep, tile);
+        const uint32_t h = tile * kTile + (threadIdx.x & 63u);
         if (h >= rep.Vh) continue;
         Site<D> x;
         x.template from_half<true>(rep, h, p, layer);

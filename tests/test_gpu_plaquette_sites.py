@@ -40,3 +40,18 @@ def test_batch_of_several_shapes(oracle_mod):
         o = oracle_mod.Lattice(list(s), seed=seed)
         o.set_links(b.get_links(r))
         assert np.allclose(got[r], o.plaquette(beta), rtol=1e-12, atol=1e-13, equal_nan=True), s
+
+
+@pytest.mark.parametrize("ext,nlat,mask,prec", [
+    ([16, 12, 12, 30], 1, 0, su3hb.FP64_18), ([32, 2, 4, 258], 1, 0, su3hb.FP32_18),      # three strips; one of one tile
+    ([16, 8, 20, 26], 2, 0b1010, su3hb.FP32_12), ([16, 16, 18, 16], 1, 0, su3hb.FP64_12),  # two layers; a cut strip
+    ([14, 10, 20, 24], 1, 0, su3hb.FP32_18),                                              # rows that cut a tile
+    ([8, 8, 4, 8, 32], 1, 0, su3hb.FP64_12), ([4, 4, 4, 4, 8, 32], 1, 0, su3hb.FP32_12),
+])
+def test_strips_take_every_site_once(oracle_mod, ext, nlat, mask, prec):
+    g = su3hb.Lattice(ext, nlat=nlat, dlt_mask=mask, precision=prec, seed=9)
+    o = oracle_mod.Lattice(ext, nlat=nlat, dlt_mask=mask, seed=9)
+    o.set_links(g.get_links())
+    # a site taken twice for another changes the averages by 1 / (number of
+    # plaquettes), above 1e-7 here; rounding stays below 1e-12
+    assert np.allclose(g.plaquette(5.0, 5.6)[:5], o.plaquette(5.0, 5.6)[:5], rtol=1e-12, atol=1e-13, equal_nan=True)
