@@ -114,7 +114,7 @@ __global__ void __launch_bounds__(256) plaquette_kernel(PlaqArgs a)
 // parity of the same ones; XCD k takes a contiguous run of blocks.  The loops
 // over the planes stay loops: unrolled, every plane's loads are hoisted.  Per
 // plane of the lattice (plaquette_kernel) every link crossed the memory side
-// D - 1 times: 32^4 FP64-12 330 -> 160 us.
+// D - 1 times: 32^4 FP64-12 330 -> 160 us with the order below.
 // Strips: from four dimensions on the tiles go kPlaqStrip steps of x_{D-2} at
 // a time along the whole of x_{D-1}, where such a strip's row is whole tiles.
 // Lexicographically, the links at x + e_{D-1} lay a whole x_{D-1} layer ahead
@@ -174,6 +174,14 @@ __global__ void __launch_bounds__(256, 2) plaquette_site_kernel(PlaqArgs a)
                 const mat3<R> b = load_link<PREC>(link_ref<D, PREC>(links, rep, l_pm, nu, q, s_pm));
                 const mat3<R> c = load_link<PREC>(link_ref<D, PREC>(links, rep, layer, nu, p, x.s));
                 const mat3<R> d = load_link<PREC>(link_ref<D, PREC>(links, rep, l_pn, mu, q, s_pn));
+                // FP64-18: all loads before the first product.  Left to itself the
+                // compiler put them between the products, one link in flight at
+                // a time; the registers this takes leave two waves per SIMD for
+                // three (32^4 303 -> 236 us, 64^3 x 32 2542 -> 2397 us).  The
+                // other storages lose more by that than they gain (64^3 x 32
+                // FP32-18 1010 -> 1076, FP32-12 860 -> 875, FP64-12 1343 ->
+                // 1374 us).
+                if constexpr (PREC == kFP64_18) __builtin_amdgcn_sched_barrier(0);
                 const double P = re_tr_na(mul_nn(widen<double>(umu), widen<double>(b)),
                                           mul_nn(widen<double>(c), widen<double>(d))) *
                                  (1.0 / 3.0);
