@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -12,6 +13,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "su3hb.h"
@@ -50,6 +52,18 @@ constexpr int kPlaqBlock = 256;
 constexpr uint64_t kPlaqBySite = uint64_t(1) << 16;
 constexpr uint32_t kSeriesCap = 4096;
 constexpr size_t kStageBytes = size_t(256) << 20;
+// Large copies to and from pageable host memory go through a ring of pinned
+// slots, which a few threads fill or empty while the copy engine works on the
+// others; the runtime's own copy is one thread's.  get_links, whose destination
+// is often touched for the first time: 5.1 MB 345 -> 192 us, 11.4 MB 705 -> 385,
+// 36 MB 3890 -> 1190, 576 MB 57 -> 14 ms; below 4 MB starting threads costs what they
+// save (2.3 MB 169 -> 150 us).  set_links: 36 MB 1390 -> 1130 us, 182 MB 6.9 -> 4.9 ms,
+// 576 MB 42 -> 29 ms; at 18 MB the runtime's copy is level (636 and 680 us).  Two
+// threads more than four pay where the copy is long (36 MB from the device 1710
+// -> 1190 us, 5 MB 192 -> 226 us).
+constexpr size_t kRingSlot = size_t(4) << 20, kRingPart = size_t(256) << 10;
+constexpr uint32_t kRingSlots = 4, kRingThreads = 6;
+constexpr size_t kRingMinDown = size_t(4) << 20, kRingMinUp = size_t(32) << 20;
 constexpr size_t kMeasBytes = size_t(64) << 20;  // partial sums kept before they are added up
 
 }  // namespace
@@ -83,6 +97,8 @@ struct su3hb_lattice {
     bool stats_dirty = true;      // the slots hold counts that no call has read
     unsigned long long *d_maxdef = nullptr;
     double *d_stage = nullptr;
+    void *ring = nullptr;         // pinned slots of large copies, from the first one on
+    hipEvent_t ring_events[kRingSlots] = {};
     uint32_t *d_bar = nullptr;    // grid-barrier counters of persistent launches
     int block = 256, order = 1, waves = kDefaultWaves;  // default_shape
     bool shape_set = false;       // by su3hb_set_launch or the tuner
@@ -286,6 +302,9 @@ void destroy(su3hb_lattice *L)
     hipFree(L->d_tables);
     hipFree(L->d_meas);
     hipFree(L->d_stage);
+    for (auto e : L->ring_events)
+        if (e) hipEventDestroy(e);
+    if (L->ring) hipHostFree(L->ring);
     hipHostFree(L->host);
     delete L;
 }
@@ -595,16 +614,21 @@ int check_small(const su3hb_lattice *L)
     return SU3HB_OK;
 }
 
+// The null stream cannot be captured.
+int refuse_capture(const su3hb_lattice *L)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (L->stream) HIPCHK(hipStreamIsCapturing(L->stream, &capture));
+    return capture == hipStreamCaptureStatusNone ? SU3HB_OK : fail(SU3HB_EHIP, "the stream is being captured");
+}
+
 int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measure, bool counters)
 {
     if (n <= 0) return SU3HB_OK;
     if (int rc = check_sweep_room(L, n)) return rc;
     // a captured call could be replayed, with sweeps that this handle would not
-    // count (su3hb_sweep_measure_static is the call for that); the null stream
-    // cannot be captured
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (L->stream) HIPCHK(hipStreamIsCapturing(L->stream, &capture));
-    if (capture != hipStreamCaptureStatusNone) return fail(SU3HB_EHIP, "the stream is being captured");
+    // count (su3hb_sweep_measure_static is the call for that)
+    if (int rc = refuse_capture(L)) return rc;
     if (use_small(L)) {
         if (int rc = run_small(L, b0, b1, nhit, n, measure, counters)) return rc;
     } else {
@@ -659,6 +683,120 @@ int ensure_stage(su3hb_lattice *L)
     return SU3HB_OK;
 }
 
+bool is_pageable(const void *p)
+{
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) == hipSuccess) return at.type == hipMemoryTypeUnregistered;
+    (void)hipGetLastError();
+    return true;
+}
+
+bool have_ring(su3hb_lattice *L)
+{
+    bool ok = true;
+    for (auto &e : L->ring_events)
+        if (!e) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!L->ring) ok = ok && hipHostMalloc(&L->ring, kRingSlot * kRingSlots, 0) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    return ok;
+}
+
+// This thread makes all calls of the runtime, the threads it starts copy parts
+// of pieces.  Piece c uses slot c % kRingSlots; the threads have it while
+// open > c and not all its parts are copied, else the copy engine has it.
+// Returns with the copy complete, or kNoRing with nothing done.
+constexpr int kNoRing = 1;
+int ring_copy(su3hb_lattice *L, char *host, char *dev, size_t bytes, bool to_device)
+{
+    // events of a captured stream never end
+    if (int rc = refuse_capture(L)) return rc;
+    if (!have_ring(L)) return kNoRing;
+    const uint32_t n = uint32_t((bytes + kRingSlot - 1) / kRingSlot);
+    char *ring = static_cast<char *>(L->ring);
+    auto size_of = [=](uint32_t c) { return std::min(kRingSlot, bytes - size_t(c) * kRingSlot); };
+    auto slot_of = [=](uint32_t c) { return ring + size_t(c % kRingSlots) * kRingSlot; };
+    constexpr uint32_t P = uint32_t(kRingSlot / kRingPart);
+    const uint32_t parts = uint32_t((bytes + kRingPart - 1) / kRingPart);
+    std::atomic<uint32_t> copied[kRingSlots] = {}, next{0}, open{to_device ? kRingSlots : 0u};
+    std::atomic<bool> stop{false};
+    auto copies = [&] {
+        for (uint32_t j; (j = next.fetch_add(1)) < parts;) {
+            const uint32_t c = j / P;
+            while (open.load(std::memory_order_acquire) <= c) {
+                if (stop.load()) return;
+                std::this_thread::yield();
+            }
+            const size_t at = size_t(j) * kRingPart, size = std::min(kRingPart, bytes - at);
+            char *h = host + at, *s = slot_of(c) + size_t(j % P) * kRingPart;
+            if (to_device) std::memcpy(s, h, size);
+            else std::memcpy(h, s, size);
+            copied[c % kRingSlots].fetch_add(1, std::memory_order_release);
+        }
+    };
+    std::thread threads[kRingThreads];
+    const uint32_t want = bytes >= kRingMinUp ? kRingThreads : kRingThreads - 2;
+    uint32_t started = 0;
+    try {
+        for (; started < want; ++started) threads[started] = std::thread(copies);
+    } catch (...) {
+        if (!started) return kNoRing;
+    }
+    auto was_copied = [&](uint32_t c) {
+        const uint32_t all = c / kRingSlots * P + std::min(P, parts - c * P);
+        return copied[c % kRingSlots].load(std::memory_order_acquire) == all;
+    };
+    hipError_t e = hipSuccess;
+    for (uint32_t issued = 0, ended = 0; ended < n && e == hipSuccess;) {
+        if (issued < n && (to_device ? was_copied(issued)
+                                     : issued < kRingSlots || was_copied(issued - kRingSlots))) {
+            char *d = dev + size_t(issued) * kRingSlot;
+            e = to_device ? hipMemcpyAsync(d, slot_of(issued), size_of(issued), hipMemcpyHostToDevice, L->stream)
+                          : hipMemcpyAsync(slot_of(issued), d, size_of(issued), hipMemcpyDeviceToHost, L->stream);
+            if (e == hipSuccess) e = hipEventRecord(L->ring_events[issued % kRingSlots], L->stream);
+            ++issued;
+        } else if (ended == issued) {
+            std::this_thread::yield();
+        }
+        if (e == hipSuccess && ended < issued) {
+            const hipError_t q = hipEventQuery(L->ring_events[ended % kRingSlots]);
+            if (q == hipSuccess) open.store(++ended + (to_device ? kRingSlots : 0u), std::memory_order_release);
+            else if (q != hipErrorNotReady) e = q;
+        }
+    }
+    if (e != hipSuccess) stop.store(true);
+    for (uint32_t i = 0; i < started; ++i) threads[i].join();
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(L->stream);
+        return fail(SU3HB_EHIP, "copy of links: %s", hipGetErrorString(e));
+    }
+    return SU3HB_OK;
+}
+
+// Links in the canonical layout to and from the staging buffer, in stream
+// order; the one from the device is complete on return.
+int upload_stage(su3hb_lattice *L, const double *host, size_t bytes)
+{
+    if (bytes >= kRingMinUp && is_pageable(host)) {
+        const int rc = ring_copy(L, const_cast<char *>(reinterpret_cast<const char *>(host)),
+                                 reinterpret_cast<char *>(L->d_stage), bytes, true);
+        if (rc != kNoRing) return rc;
+    }
+    HIPCHK(hipMemcpyAsync(L->d_stage, host, bytes, hipMemcpyHostToDevice, L->stream));
+    return SU3HB_OK;
+}
+
+int download_stage(su3hb_lattice *L, double *host, size_t bytes)
+{
+    if (bytes >= kRingMinDown && is_pageable(host)) {
+        const int rc =
+            ring_copy(L, reinterpret_cast<char *>(host), reinterpret_cast<char *>(L->d_stage), bytes, false);
+        if (rc != kNoRing) return rc;
+    }
+    HIPCHK(hipMemcpyAsync(host, L->d_stage, bytes, hipMemcpyDeviceToHost, L->stream));
+    HIPCHK(hipStreamSynchronize(L->stream));
+    return SU3HB_OK;
+}
+
 int get_replica_links(su3hb_lattice *L, int r, double *host, size_t n)
 {
     const RepDesc &rep = L->reps[r];
@@ -673,9 +811,7 @@ int get_replica_links(su3hb_lattice *L, int r, double *host, size_t n)
     for (uint64_t c0 = 0; c0 < nsites; c0 += chunk) {
         const uint32_t cnt = uint32_t(std::min<uint64_t>(chunk, nsites - c0));
         HIPCHK(launch_pack(L->nd, L->prec, L->stream, L->links, L->d_reps, r, c0, cnt, L->d_stage));
-        HIPCHK(hipMemcpyAsync(host + c0 * per_site, L->d_stage, size_t(cnt) * per_site * sizeof(double),
-                              hipMemcpyDeviceToHost, L->stream));
-        HIPCHK(hipStreamSynchronize(L->stream));
+        if (int rc = download_stage(L, host + c0 * per_site, size_t(cnt) * per_site * sizeof(double))) return rc;
     }
     return check_small(L);
 }
@@ -697,8 +833,7 @@ int set_replica_links(su3hb_lattice *L, int r, const double *host, size_t n)
     HIPCHK(launch_u64_zero(L->stream, L->d_maxdef, 1));
     for (uint64_t c0 = 0; c0 < nsites; c0 += chunk) {
         const uint32_t cnt = uint32_t(std::min<uint64_t>(chunk, nsites - c0));
-        HIPCHK(hipMemcpyAsync(L->d_stage, host + c0 * per_site, size_t(cnt) * per_site * sizeof(double),
-                              hipMemcpyHostToDevice, L->stream));
+        if (int rc = upload_stage(L, host + c0 * per_site, size_t(cnt) * per_site * sizeof(double))) return rc;
         HIPCHK(launch_validate(L->stream, L->d_stage, uint64_t(cnt) * L->nd, L->d_maxdef));
         if (!single) HIPCHK(hipStreamSynchronize(L->stream));
     }
@@ -713,8 +848,7 @@ int set_replica_links(su3hb_lattice *L, int r, const double *host, size_t n)
     for (uint64_t c0 = 0; c0 < nsites; c0 += chunk) {
         const uint32_t cnt = uint32_t(std::min<uint64_t>(chunk, nsites - c0));
         if (!single)
-            HIPCHK(hipMemcpyAsync(L->d_stage, host + c0 * per_site, size_t(cnt) * per_site * sizeof(double),
-                                  hipMemcpyHostToDevice, L->stream));
+            if (int rc = upload_stage(L, host + c0 * per_site, size_t(cnt) * per_site * sizeof(double))) return rc;
         HIPCHK(launch_unpack(L->nd, L->prec, L->stream, L->links, L->d_reps, r, c0, cnt, L->d_stage));
         HIPCHK(hipStreamSynchronize(L->stream));
     }
