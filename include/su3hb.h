@@ -206,8 +206,8 @@ int su3hb_set_state(su3hb_lattice *lat, uint64_t seed, uint64_t sweep);
  * 3 for D = 4; 4 for D = 4 with FP32 links.  Results are bit-identical for
  * every shape.  get_launch reports the order in effect (with the 8 and 16).
  * Until a shape is set (here or by su3hb_autotune), lattices and batches whose
- * slices hold at most 32768 links share every link's update between lanes and
- * waves, and calls on those of at most 1024 links per slice run all their
+ * slices hold few links (from 20480 to 49152 by dimension and precision) share
+ * every link's update between lanes or waves, and calls on those of at most 1024 links per slice run all their
  * sweeps in one launch (in blocks of one XCD that wait for each other's
  * slices; a wait past its limit ends the launch, and the next call that
  * synchronises returns SU3HB_EHIP).  The shape then stands for nothing.

@@ -14,7 +14,8 @@ BUILD = os.path.join(ROOT, "_build")
 DIMS = range(2, 7)
 # (source, object, flags): the update kernels are compiled once per dimension
 UNITS = [(f"{src}.hip", f"{src}{d}", [f"-DSU3HB_DIM={d}"]) for src in ("update", "update_split") for d in DIMS]
-UNITS += [(f"{src}.hip", src, []) for src in ("update", "update_split", "aux")] + [("capi.cpp", "capi", [])]
+UNITS += [("update_planes.hip", f"update_planes{d}", [f"-DSU3HB_DIM={d}"]) for d in (3, 4)]
+UNITS += [(f"{src}.hip", src, []) for src in ("update", "update_split", "update_planes", "aux")] + [("capi.cpp", "capi", [])]
 ARCH = os.environ.get("SU3HB_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

@@ -104,6 +104,7 @@ struct su3hb_lattice {
     bool shape_set = false;       // by su3hb_set_launch or the tuner
     bool plq_by_site = false;     // plaquette launches: one thread per site
     uint32_t split_groups = 0;    // blocks of 16 links (split.h) in a slice
+    uint32_t planes_blocks = 0;   // blocks of 64 links (update_planes.hip) in a slice
     uint32_t *d_work = nullptr;   // queues of launches that hold whole sweeps
     uint32_t small_launches = 0;  // such launches so far
     uint32_t upd_blocks = 0, plq_blocks = 0, pers_blocks = 0;
@@ -123,7 +124,7 @@ constexpr int kOrderStage = 16;
 std::mutex g_tune_mu;
 struct Shape {
     int block, order, waves;
-    bool automatic;  // left to use_split
+    bool automatic;  // left to slice_form
 };
 std::map<std::string, Shape> g_tune_cache;
 
@@ -156,7 +157,7 @@ void layout_reps(su3hb_lattice *L)
     uint64_t off = 0, sites = 0;
     for (auto &r : L->reps) sites += uint64_t(r.nlat) * r.V;
     L->plq_by_site = sites >= kPlaqBySite;
-    uint32_t ub = 0, pb = 0, sb = 0, gb = 0;
+    uint32_t ub = 0, pb = 0, sb = 0, gb = 0, lb = 0;
     const int NE = elems_per_link(L->prec);
     for (auto &r : L->reps) {
         r.elem_offset = off;
@@ -177,10 +178,13 @@ void layout_reps(su3hb_lattice *L)
         r.pers_block0 = sb;
         r.pers_blocks = (r.nlat * r.Vh + kPersistentThreads - 1) / kPersistentThreads;
         sb += r.pers_blocks;
+        r.planes_block0 = lb;
+        lb += (r.nlat * r.Vh + kPlanesLinks - 1) / kPlanesLinks;
         r.split_group0 = gb;
         gb += (r.nlat * r.Vh + kSplitLinks - 1) / kSplitLinks;
     }
     L->split_groups = gb;
+    L->planes_blocks = lb;
     L->upd_blocks = ub;
     L->plq_blocks = pb;
     L->pers_blocks = sb;
@@ -387,14 +391,31 @@ int effective_order(const su3hb_lattice *L)
     return base_order(L) | (L->order & kOrderReverse) | (stage_applies(L) ? kOrderStage : 0);
 }
 
-// Slices that share every link's update between lanes and waves, and calls that
-// hold whole sweeps in one launch (the lines are drawn in layout.h): unless the
-// caller or the tuner chose a launch shape.
-bool use_split(const su3hb_lattice *L) { return !L->shape_set && L->split_groups <= kSplitGroups; }
+// How a slice's links are given to threads (the lines are drawn in layout.h).
+enum class Form { kShared, kPlanes, kThread };
+
+Form slice_form(int D, int prec, uint32_t split_groups, uint32_t planes_blocks)
+{
+    if (split_groups <= shared_most(D, prec) / kSplitLinks) return Form::kShared;
+    return planes_blocks <= planes_most(D, prec) ? Form::kPlanes : Form::kThread;
+}
+
+// Unless the caller or the tuner chose a launch shape, which is one of a thread
+// per link.
+Form slice_form(const su3hb_lattice *L)
+{
+    return L->shape_set ? Form::kThread : slice_form(L->nd, L->prec, L->split_groups, L->planes_blocks);
+}
+
+// Calls that hold whole sweeps in one launch.
 bool use_small(const su3hb_lattice *L) { return !L->shape_set && L->split_groups <= kSmallGroups; }
 
-// Blocks that write partial sums in a measured slice.
-uint32_t meas_blocks(const su3hb_lattice *L) { return use_split(L) ? L->split_groups : L->upd_blocks; }
+// Blocks of a slice, which write partial sums in a measured one.
+uint32_t slice_blocks(const su3hb_lattice *L)
+{
+    const Form f = slice_form(L);
+    return f == Form::kShared ? L->split_groups : f == Form::kPlanes ? L->planes_blocks : L->upd_blocks;
+}
 
 UpdateArgs update_args(const su3hb_lattice *L, double b0, double b1, int nhit, bool counters)
 {
@@ -474,7 +495,7 @@ int meas_classes(const su3hb_lattice *L) { return L->reps[0].nlat == 2 ? 3 : 1; 
 // Doubles of partial sums that one measured sweep writes.
 size_t meas_doubles(const su3hb_lattice *L)
 {
-    return size_t(L->nd) * meas_blocks(L) * size_t(meas_classes(L));
+    return size_t(L->nd) * slice_blocks(L) * size_t(meas_classes(L));
 }
 
 // Room for the partial sums of n sweeps, or of as many as kMeasBytes hold
@@ -506,9 +527,8 @@ int sweep_args(const su3hb_lattice *L, double b0, double b1, int nhit, int measu
         a.meas = L->d_meas;
         a.meas_classes = meas_classes(L);
     }
-    if (use_split(L)) {
-        a.total_blocks = L->split_groups;
-    } else {
+    a.total_blocks = slice_blocks(L);
+    if (slice_form(L) == Form::kThread) {
         // the largest LDS request of the sweep (a measured parity-1 slice)
         // must fit one block's share of the compute unit
         UpdateArgs m = a;
@@ -534,7 +554,7 @@ int enqueue_sweep(su3hb_lattice *L, const UpdateArgs &first, std::vector<int> *t
                   size_t *ev = nullptr)
 {
     UpdateArgs a = first;
-    const bool split = use_split(L);
+    const Form form = slice_form(L);
     const dim3 grid = update_grid(L), block(L->block);
     hipStream_t st = L->stream;
     for (int p = 0; p < 2; ++p)
@@ -543,7 +563,8 @@ int enqueue_sweep(su3hb_lattice *L, const UpdateArgs &first, std::vector<int> *t
             a.mu = mu;
             a.reverse = (L->order & kOrderReverse) && ((p * L->nd + mu) & 1) ? 1 : 0;
             if (timed) HIPCHK(hipEventRecord(L->events[(*ev)++], st));
-            if (split) HIPCHK(launch_update_split(L->nd, L->prec, st, a));
+            if (form == Form::kShared) HIPCHK(launch_update_split(L->nd, L->prec, st, a));
+            else if (form == Form::kPlanes) HIPCHK(launch_update_planes(L->nd, L->prec, st, a));
             else HIPCHK(launch_update(L->nd, L->prec, L->waves, grid, block, st, a));
             if (timed) {
                 HIPCHK(hipEventRecord(L->events[(*ev)++], st));
@@ -557,7 +578,7 @@ int enqueue_sweep(su3hb_lattice *L, const UpdateArgs &first, std::vector<int> *t
 // of the series.
 int finish_measure(su3hb_lattice *L, double b0, double b1, int n, double *series)
 {
-    HIPCHK(launch_measure_finalize(L->stream, L->d_meas, n, L->nd, meas_blocks(L), meas_classes(L),
+    HIPCHK(launch_measure_finalize(L->stream, L->d_meas, n, L->nd, slice_blocks(L), meas_classes(L),
                                    double(L->reps[0].V), int(L->reps[0].nlat), b0, b1, series, L->d_sweep));
     return SU3HB_OK;
 }
@@ -1181,7 +1202,8 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     // D = 4; orders 2 to 6 only where they apply (otherwise they would repeat
     // another order), orders 3, 5 and 6 only with more than one wave per block
     std::vector<Shape> cands;
-    if (L->split_groups <= kSplitGroups) cands.push_back(default_shape(L->nd, L->prec));
+    if (slice_form(L->nd, L->prec, L->split_groups, L->planes_blocks) != Form::kThread)
+        cands.push_back(default_shape(L->nd, L->prec));
     for (int waves : {2, 3, 4}) {
         if (waves >= 3 && L->nd != 4) continue;
         if (waves == 4 && !is_fp32(L->prec)) continue;
@@ -1511,8 +1533,9 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     const int nc = p->nlat == 2 ? 3 : 1;
     // small slices as in a handle whose launch shape was not set
     const uint32_t groups = (rep.nlat * rep.Vh + kSplitLinks - 1) / kSplitLinks;
-    const bool split = groups <= kSplitGroups;
-    const uint32_t blocks = split ? groups : rep.upd_blocks;
+    const uint32_t planes = (rep.nlat * rep.Vh + kPlanesLinks - 1) / kPlanesLinks;
+    const Form form = slice_form(p->nd, p->precision, groups, planes);
+    const uint32_t blocks = form == Form::kShared ? groups : form == Form::kPlanes ? planes : rep.upd_blocks;
     const size_t meas_doubles = size_t(p->nd) * blocks * size_t(nc);
     if (series && meas_doubles > kScratchMeasDoubles)
         return fail(SU3HB_EINVAL,
@@ -1543,7 +1566,7 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
     a.total_blocks = blocks;
     a.meas = series ? d_meas : nullptr;
     const dim3 grid((rep.upd_blocks + 7) / 8 * 8), block(kBlock);
-    if (!split) {
+    if (form == Form::kThread) {
         UpdateArgs m = a;
         m.parity = 1;
         size_t need = 0, limit = 0;
@@ -1563,7 +1586,8 @@ int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1
             for (int mu = 0; mu < p->nd; ++mu) {
                 a.parity = par;
                 a.mu = mu;
-                if (split) HIPCHK(launch_update_split(p->nd, p->precision, st, a));
+                if (form == Form::kShared) HIPCHK(launch_update_split(p->nd, p->precision, st, a));
+                else if (form == Form::kPlanes) HIPCHK(launch_update_planes(p->nd, p->precision, st, a));
                 else HIPCHK(launch_update(p->nd, p->precision, kDefaultWaves, grid, block, st, a));
             }
         const int done = sw % run + 1;

@@ -9,14 +9,15 @@ namespace su3hb {
 
 // Block partitions of the replicas: per-slice update launches, plaquette
 // launches, persistent launches, launches that share a link's update between
-// lanes (split.h).
-enum BlockKind { kUpdateBlocks = 0, kPlaquetteBlocks = 1, kPersistentBlocks = 2, kSplitBlocks = 3 };
+// lanes (split.h), launches that give planes to waves (update_planes.hip).
+enum BlockKind { kUpdateBlocks = 0, kPlaquetteBlocks = 1, kPersistentBlocks = 2, kSplitBlocks = 3, kPlanesBlocks = 4 };
 
 __device__ __forceinline__ uint32_t first_block(const RepDesc &r, int kind)
 {
     return kind == kPlaquetteBlocks    ? r.plq_block0
            : kind == kPersistentBlocks ? r.pers_block0
            : kind == kSplitBlocks      ? r.split_group0
+           : kind == kPlanesBlocks     ? r.planes_block0
                                        : r.upd_block0;
 }
 

@@ -16,6 +16,10 @@ hipError_t launch_update(int D, int prec, int waves, dim3 grid, dim3 block, hipS
 // (split.h); a.total_blocks counts blocks of kSplitLinks links
 hipError_t launch_update_split(int D, int prec, hipStream_t st, const UpdateArgs &a);
 
+// the same slice with the planes of a link's staple on waves of their own
+// (update_planes.hip); a.total_blocks counts blocks of kPlanesLinks links
+hipError_t launch_update_planes(int D, int prec, hipStream_t st, const UpdateArgs &a);
+
 // whole sweeps of a small lattice or batch in one launch
 hipError_t launch_update_small(int D, int prec, hipStream_t st, const SmallArgs &s);
 

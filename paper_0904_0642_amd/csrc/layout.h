@@ -63,6 +63,7 @@ struct RepDesc {
     uint32_t plq_spt;        // plaquettes (or sites) per thread in the plaquette launch
     uint32_t pers_block0;    // first block in a persistent launch (kPersistentThreads links per block)
     uint32_t pers_blocks;
+    uint32_t planes_block0;  // first block in a launch that gives planes to waves (kPlanesLinks links per block)
     uint32_t split_group0;   // first block in a launch that shares links between lanes (kSplitLinks links per block)
     DivMagic div[kMaxD - 1];  // division by n0 / 2 (entry 0) and by n_i (entry i, 0 < i < D - 1)
 };
@@ -100,16 +101,37 @@ constexpr uint32_t kBarrierSpinLimit = 1u << 22;
 // slices); adding them up sets word 2 back to 0.
 constexpr int kSweepWords = 4;
 
-// Launches that share a link's update between lanes and waves (split.h): links
-// of a block; blocks ("groups") of a slice up to which the library takes them
-// by itself.  Time of a slice, one thread per link -> shared, FP64-18 / FP32-12:
-// 2048 links 14.9 -> 6.9 / 13.1 -> 6.4 us, 8192 links 15.6 -> 8.0 / 13.5 ->
-// 6.9 us, 24576 links 17.6 -> 13.6 / 13.3 -> 9.5 us, 32768 links 18.2 -> 16.7 /
-// 13.3 -> 11.1 us.  The shared form does twice the work per link, so where the
-// other fills the chip it loses (51840 links: 20.4 and 13.9 us one thread per
-// link).
+// The three forms of a slice, and the lines between them.  One thread per link
+// (update.hip) has the least work in all but leaves SIMDs idle where links are
+// few; a link's update shared by lanes and waves (split.h, kSplitLinks links of
+// a block) has the shortest chain and twice the work; planes of its staple on
+// waves of their own (update_planes.hip, kPlanesLinks links of a block, D = 3 and
+// 4) lie between.  Time of a slice, shared / planes / thread, us:
+//   4D links   FP64-18           FP32-12
+//    8192       8.2  9.9 15.1     7.2  8.5 13.2
+//   20480      11.8 11.9 16.6     9.1  9.5 12.7
+//   24576      13.8 12.3 17.0     9.8  9.8 12.7
+//   32768      16.7 13.6 17.6    11.5  9.9 13.0
+//   41472      20.3 20.2 18.4    13.0 11.1 13.0
+//   49152      22.4 23.5 19.7    14.3 11.3 13.3
+//   51840      23.6 24.4 20.0    14.9 13.6 13.2
+//   3D: 24576  12.9 13.0 13.7    10.3 10.9 12.3
+//       32000  15.6 13.4 14.8    12.0 11.2 12.4
+//   2D: 18432  12.5    - 13.3    10.1    - 12.4;  25088  14.6    - 13.4    11.2    - 12.5
+//   5D: 20480  14.8    - 18.9     9.5    - 14.0;  25600  19.4    - 19.6    11.2    - 14.1
+// Planes stop where the device no longer holds all blocks at once: by the
+// registers two (FP64) and three (FP32) on each of 256 CUs.
 constexpr uint32_t kSplitLinks = 16;
-constexpr uint32_t kSplitGroups = 2048;
+constexpr uint32_t kPlanesLinks = 64;
+inline constexpr bool fp32_links(int prec) { return prec == kFP32_18 || prec == kFP32_12; }
+inline constexpr uint32_t shared_most(int D, int prec)  // links
+{
+    return D == 4 ? 20480 : D == 3 ? 24576 : fp32_links(prec) ? (D == 2 ? 28672 : 32768) : (D == 2 ? 20480 : 24576);
+}
+inline constexpr uint32_t planes_most(int D, int prec)  // blocks
+{
+    return D != 3 && D != 4 ? 0 : fp32_links(prec) ? 768 : 512;
+}
 
 // Statistics slot, padded to its own 128-byte line.
 struct alignas(128) StatSlot {

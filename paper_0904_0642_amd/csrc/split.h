@@ -136,6 +136,25 @@ __device__ __forceinline__ void rotate_column(cx<H> v[3], const cx<H> &r00, cons
     v[J] = nj;
 }
 
+// The rotation R = X V^dag of an accepted draw (su2_heatbath).
+template <typename H>
+__device__ __forceinline__ void heatbath_rotation(const double a[4], double ik, double delta, const Direction<H> &d,
+                                                  cx<H> &r00, cx<H> &r01, cx<H> &r10, cx<H> &r11)
+{
+    const double x0d = one_minus(delta);
+    const H x0 = H(x0d);
+    const H rad = sqrt_nonneg<H>(H(fmax(0.0, 1.0 - x0d * x0d)));
+    const H x1 = rad * d.sth * d.cph, x2 = rad * d.sth * d.sph, x3 = rad * d.cth;
+    const H b0 = H(a[0] * ik), b1 = H(a[1] * ik), b2 = H(a[2] * ik), b3 = H(a[3] * ik);
+    const cx<H> X00{x0, x3}, X01{x2, x1}, X10{-x2, x1}, X11{x0, -x3};
+    const cx<H> V00{b0, -b3}, V01{-b2, -b1}, V10{b2, -b1}, V11{b0, b3};
+    r00 = r01 = r10 = r11 = cx<H>{H(0), H(0)};
+    cfma(r00, X00, V00); cfma(r00, X01, V10);
+    cfma(r01, X00, V01); cfma(r01, X01, V11);
+    cfma(r10, X10, V00); cfma(r10, X11, V10);
+    cfma(r11, X10, V01); cfma(r11, X11, V11);
+}
+
 // One subgroup heatbath on the columns u, w of a quad's link (su2_heatbath).
 // own: the lane's draws for hits 0 and 1.  Later hits are
 // tried four at a time, one per lane; the first accepted one counts, as in the
@@ -182,19 +201,8 @@ __device__ __forceinline__ void quad_heatbath(cx<H> u[3], cx<H> w[3], const Draw
     attempts += tried;
     if (!ok) return;
     ++accepts;
-    const double x0d = one_minus(delta);
-    const H x0 = H(x0d);
-    const H rad = sqrt_nonneg<H>(H(fmax(0.0, 1.0 - x0d * x0d)));
-    const H x1 = rad * v.d.sth * v.d.cph, x2 = rad * v.d.sth * v.d.sph, x3 = rad * v.d.cth;
-    const H b0 = H(a[0] * ik), b1 = H(a[1] * ik), b2 = H(a[2] * ik), b3 = H(a[3] * ik);
-    const cx<H> X00{x0, x3}, X01{x2, x1}, X10{-x2, x1}, X11{x0, -x3};
-    const cx<H> V00{b0, -b3}, V01{-b2, -b1}, V10{b2, -b1}, V11{b0, b3};
-    const H z = H(0);
-    cx<H> r00{z, z}, r01{z, z}, r10{z, z}, r11{z, z};
-    cfma(r00, X00, V00); cfma(r00, X01, V10);
-    cfma(r01, X00, V01); cfma(r01, X01, V11);
-    cfma(r10, X10, V00); cfma(r10, X11, V10);
-    cfma(r11, X10, V01); cfma(r11, X11, V11);
+    cx<H> r00, r01, r10, r11;
+    heatbath_rotation<H>(a, ik, delta, v.d, r00, r01, r10, r11);
     rotate_column<H, I, J>(u, r00, r01, r10, r11);
     rotate_column<H, I, J>(w, r00, r01, r10, r11);
 }
@@ -582,13 +590,13 @@ __device__ __forceinline__ void split_update(const UpdateArgs &a, const RepDesc 
 
 // A wave's counters into a slot of the statistics, its measurement into the
 // partial sums of its group, of the place-th measured sweep.
-template <int D, int NC>
+template <int D, int NC, int FIRST = 4>
 __device__ __forceinline__ void split_flush(const UpdateArgs &a, uint32_t group, uint32_t place, SplitSums<NC> &v)
 {
     const uint32_t lane = threadIdx.x & 63u;
     if (a.meas != nullptr && a.parity == 1) {
 #pragma unroll
-        for (int off = 4; off < 64; off <<= 1)
+        for (int off = FIRST; off < 64; off <<= 1)
 #pragma unroll
             for (int k = 0; k < NC; ++k) v.plaq[k] += __shfl_xor(v.plaq[k], off);
         if (lane == 0) {
@@ -599,7 +607,7 @@ __device__ __forceinline__ void split_flush(const UpdateArgs &a, uint32_t group,
     }
     if (a.stats == nullptr) return;
 #pragma unroll
-    for (int off = 4; off < 64; off <<= 1) {
+    for (int off = FIRST; off < 64; off <<= 1) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             v.att[i] += __shfl_xor(v.att[i], off);
