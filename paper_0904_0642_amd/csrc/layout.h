@@ -152,6 +152,8 @@ struct UpdateArgs {
     int order;                   // 0 hardware, 1 XCD-contiguous, 2 and 4 XCD slabs, 3, 5 and 6 XCD slabs of 3D blocks,
                                  // 7 XCD slabs of 4D wave tiles
     int reverse;                 // 1: each XCD walks its blocks last to first (alternate slices)
+    uint32_t strip_row;          // order 1: the logical blocks go in strips (set_strips in capi.cpp): waves of a
+    uint32_t strips, strip_last; // strip's row (0: no strips), strips, rows of a strip
     uint32_t slab;               // orders 2, 3: tiles of the last direction per XCD
     uint32_t cp;                 // orders 2, 3: blocks (order 3: waves) per (x_{D-2}, x_{D-1}) plane
     uint32_t n2;                 // orders 2, 3: extent of direction D-2

@@ -307,6 +307,18 @@ __device__ __forceinline__ void flush_stats(const UpdateArgs &a, uint32_t lb, in
     __syncthreads();  // the shared arrays are reused by the next block in a persistent loop
 }
 
+// The link of a thread whose place in the walk is lt, where the walk goes in
+// strips of x_{D-2} along the whole of x_{D-1}: whole waves of 64 links change
+// places within their layer.
+__device__ __forceinline__ uint32_t strip_link(const UpdateArgs &a, const RepDesc &rep, uint32_t lt)
+{
+    const uint32_t w = __builtin_amdgcn_readfirstlane(lt >> 6), tiles = rep.Vh >> 6;
+    if (w >= rep.nlat * tiles) return lt;
+    const uint32_t first = w >= tiles ? tiles : 0u, t = w - first, per = a.strip_row * a.strip_last;
+    const uint32_t strip = t / per, rem = t - strip * per, x = rem / a.strip_row;
+    return ((x * a.strips + strip) * a.strip_row + (rem - x * a.strip_row) + first) * 64u + (lt & 63u);
+}
+
 // Update the links of logical block lb (replica found by binary search),
 // adding to the thread's counters; lt_override >= 0 gives the thread's link
 // directly (order 3).
@@ -359,10 +371,11 @@ __device__ __forceinline__ void block_links(const UpdateArgs &a, uint32_t lb, ui
         const int kind = a.persistent ? kPersistentBlocks : kUpdateBlocks;
         const int r = a.nrep == 1 ? 0 : find_replica(a.reps, a.nrep, lb, kind);
         const RepDesc &rep = a.reps[r];
-        const uint32_t lt = lt_override >= 0 ? uint32_t(lt_override)
+        uint32_t lt = lt_override >= 0 ? uint32_t(lt_override)
                                              : (lb - first_block(rep, kind)) * blockDim.x + threadIdx.x;
         const cx<typename Store<PREC>::real> *stg = nullptr;
         int32_t stg_lo = 0;
+        if (lt_override < 0 && a.strip_row) lt = strip_link(a, rep, lt);
         if constexpr (NC == 1) {
             if (a.stage) stg = stage_wave<D, PREC>(a, rep, lt, stg_lo);
         }
