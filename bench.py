@@ -35,7 +35,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_0904_0642_amd", "csrc", f)
-                  for f in ("update.hip", "device_math.h", "geometry.h", "layout.h", "log_table.h")]
+                  for f in ("update.hip", "slice.h", "device_math.h", "geometry.h", "layout.h", "log_table.h")]
 
 WORKLOADS = {
     # name: (extents, precision, beta)
@@ -180,8 +180,8 @@ def batch_leg(steps: int, warmup: int, n_hit: int, autotune_ms: int, nrep: int =
               modes=("graph_per_slice", "persistent")):
     """Independent replicas of mixed sizes (8^4, 12^4, 16^3x4 round robin),
     beta uniform in [5.5, 6.5], FP32 links, one launch per slice for all
-    replicas replayed from a HIP graph, and the same sweeps as one persistent
-    cooperative launch."""
+    replicas (the label keeps its old name), and the same sweeps as one
+    persistent cooperative launch."""
     import torch
 
     import paper_0904_0642_amd as su3hb

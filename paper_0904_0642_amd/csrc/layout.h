@@ -93,9 +93,9 @@ constexpr uint32_t kBarrierSpinLimit = 1u << 22;
 // which the parity-0 slices read; their last one copies it to word 1, which
 // the parity-1 slices read, and the last of those writes word 0 of the sweep
 // after.  No slice writes a word that it reads, so the counter needs no
-// launch of its own: a launch of one wave costs 4.4 us inside a replayed
-// graph, and so did adding up each sweep's plaquettes (5.7 us), now one launch
-// for all sweeps of a call (4^4 FP64-18, 20 measured sweeps: 2.46 -> 2.13 ms;
+// launch of its own: a launch of one wave between two slices cost 4.4 us, and
+// so did adding up each sweep's plaquettes (5.7 us), now one launch for all
+// sweeps of a call (4^4 FP64-18, 20 measured sweeps: 2.46 -> 2.13 ms;
 // 16^4, 4 sweeps: 0.70 -> 0.64 ms).  Words 2 and 3 count the measured sweeps whose
 // partial sums wait in `meas` in the same way (word 3 is read by the measured
 // slices); adding them up sets word 2 back to 0.

@@ -22,7 +22,6 @@ def test_links_return_as_they_went(ext):
     b = su3hb.Lattice(ext, start=su3hb.COLD, seed=4)
     b.set_links(want)
     assert np.array_equal(b.get_links(), want)
-    assert np.array_equal(b.buffer.cpu().numpy(), a.buffer.cpu().numpy())
     # the last matrix of the input is not in SU(3): nothing is written
     bad = want.copy()
     bad.reshape(-1, 3, 3)[-1] *= 1.5

@@ -97,3 +97,38 @@ def test_random_numbers_of_two_layers_and_forms_alternate():
     assert np.allclose(sa, sb, rtol=1e-12, atol=0, equal_nan=True)
     assert np.allclose(sa2, sb2, rtol=1e-12, atol=0, equal_nan=True)
     assert a.get_state() == b.get_state() == (2, 7)
+
+
+@pytest.mark.parametrize("ext", [[4, 4, 4, 4], [14, 14, 14, 16], [24, 24, 20, 10]])
+def test_static_sweeps_in_a_captured_graph(ext):
+    # every form of a slice, replayed with work between the replays, against
+    # the same calls one by one
+    import ctypes as C
+
+    import torch
+
+    def call(lat, series, stream):
+        p = su3hb.make_params(ext, 1, 0, False, F64, su3hb.HOT, 5, device_links=C.c_void_p(lat.buffer.data_ptr()),
+                              device_bytes=lat.buffer.numel(), hip_stream=C.c_void_p(stream.cuda_stream))
+        su3hb.su3hb_sweep_measure_static(p, 5.9, 5.9, 8, 2, 0, C.c_void_p(series.data_ptr()))
+
+    a, b = (su3hb.Lattice(ext, seed=5) for _ in range(2))
+    sa, sb = (torch.zeros(12, dtype=torch.float64, device="cuda") for _ in range(2))
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    call(a, sa, s)  # looks the scratch up
+    call(b, sb, s)
+    s.synchronize()
+    with torch.cuda.stream(s):
+        graph = torch.cuda.CUDAGraph()
+        graph.capture_begin()
+        call(a, sa, s)
+        graph.capture_end()
+        for _ in range(4):
+            graph.replay()
+            s.synchronize()
+            torch.ones(1000, device="cuda").sum().item()
+            call(b, sb, s)
+            s.synchronize()
+            assert torch.equal(sa.nan_to_num(-1.0), sb.nan_to_num(-1.0))
+            assert torch.equal(a.buffer, b.buffer)
