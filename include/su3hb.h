@@ -217,6 +217,11 @@ int su3hb_set_state(su3hb_lattice *lat, uint64_t seed, uint64_t sweep);
 int su3hb_set_launch(su3hb_lattice *lat, int block, int order, int waves);
 int su3hb_get_launch(const su3hb_lattice *lat, int *block, int *order, int *waves);
 
+/* Polls (1 .. 2^24, which is the default and takes seconds) after which a
+ * launch that holds whole sweeps gives up a wait for another block's slice.
+ * For tests of that error; applies to the calls that follow. */
+int su3hb_set_wait_limit(su3hb_lattice *lat, unsigned polls);
+
 /* Time the candidate launch shapes on this lattice for about budget_ms (two
  * passes, each shape keeping its faster one) and
  * keep the fastest (cached per precision, D and extents for the process).

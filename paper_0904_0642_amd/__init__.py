@@ -67,6 +67,7 @@ _SIGS = {
     "su3hb_set_state": (C.c_int, [C.c_void_p, C.c_uint64, C.c_uint64]),
     "su3hb_set_launch": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int]),
     "su3hb_get_launch": (C.c_int, [C.c_void_p, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
+    "su3hb_set_wait_limit": (C.c_int, [C.c_void_p, C.c_uint]),
     "su3hb_autotune": (C.c_int, [C.c_void_p, C.c_int]),
     "su3hb_sweep_timed": (C.c_int, [C.c_void_p, C.c_double, C.c_double, C.c_int, C.c_int, C.c_int,
                                     C.POINTER(C.c_double), C.POINTER(C.c_double)]),
@@ -212,6 +213,10 @@ def su3hb_get_launch(h):
     b, o, w = C.c_int(), C.c_int(), C.c_int()
     _check(lib().su3hb_get_launch(h, C.byref(b), C.byref(o), C.byref(w)))
     return b.value, o.value, w.value
+
+
+def su3hb_set_wait_limit(h, polls):
+    _check(lib().su3hb_set_wait_limit(h, int(polls)))
 
 
 def su3hb_autotune(h, budget_ms=200):

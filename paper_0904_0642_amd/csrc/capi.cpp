@@ -107,6 +107,7 @@ struct su3hb_lattice {
     uint32_t planes_blocks = 0;   // blocks of 64 links (update_planes.hip) in a slice
     uint32_t *d_work = nullptr;   // queues of launches that hold whole sweeps
     uint32_t small_launches = 0;  // such launches so far
+    uint32_t wait_limit = kSmallSpinLimit;  // polls of a wait in them
     uint32_t upd_blocks = 0, plq_blocks = 0, pers_blocks = 0;
     std::vector<hipEvent_t> events;
     int num_cus = 0;
@@ -635,6 +636,7 @@ int run_small(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measu
     s.nlat = int(L->reps[0].nlat);
     s.series = L->host->series;
     s.failed = &L->host->failed;
+    s.spin_limit = L->wait_limit;
     const uint32_t per_sweep = 2u * uint32_t(L->nd) * L->split_groups;
     const int most = measure ? n : std::max(1, int(std::min<uint32_t>(kSeriesCap, (1u << 30) / per_sweep)));
     for (int done = 0; done < n;) {
@@ -1198,6 +1200,15 @@ int su3hb_get_launch(const su3hb_lattice *L, int *block, int *order, int *waves)
     if (block) *block = L->block;
     if (order) *order = effective_order(L);
     if (waves) *waves = L->waves;
+    return SU3HB_OK;
+}
+
+int su3hb_set_wait_limit(su3hb_lattice *L, unsigned polls)
+{
+    if (!L) return fail(SU3HB_EINVAL, "lattice is NULL");
+    if (polls < 1 || polls > kSmallSpinLimit)
+        return fail(SU3HB_EINVAL, "polls = %u outside 1..%u", polls, kSmallSpinLimit);
+    L->wait_limit = polls;
     return SU3HB_OK;
 }
 

@@ -180,7 +180,11 @@ struct UpdateArgs {
 constexpr uint32_t kSmallGroups = 64;
 constexpr uint32_t kSmallTicket = 0, kSmallXcd = 32, kSmallDone = 64, kSmallWords = kSmallDone + kSmallGroups;
 constexpr uint32_t kSmallQueues = 64;             // queues cleared together; each launch takes the next one
+// Polls until a wait for another block gives up, unless the host sets fewer.  A
+// wait for another wave of the block, which such a wait can hold up, polls LDS
+// (some 100 cycles against 1000) and has 64 times as many.
 constexpr uint32_t kSmallSpinLimit = 1u << 24;
+constexpr uint32_t kSmallLdsPolls = 64;
 
 struct SmallArgs {
     UpdateArgs u;                // total_blocks: groups of a slice
@@ -192,7 +196,8 @@ struct SmallArgs {
     int nlat;
     double *series;              // measured sweeps: 6 numbers each, in host memory
     uint32_t *work;              // kSmallWords words, zero
-    uint32_t *failed;            // host memory: set to 1 by a wait past its limit
+    uint32_t *failed;            // host memory: set to 1 by every wait past its limit
+    uint32_t spin_limit;         // polls of a wait for other blocks, at most kSmallSpinLimit
 };
 
 struct PlaqArgs {

@@ -73,7 +73,7 @@ __device__ __forceinline__ bool small_wait(const SmallArgs &s, uint32_t n, uint3
     uint32_t spins = 0;
     while (__any(lane < s.u.total_blocks &&
                  __hip_atomic_load(s.work + kSmallDone + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)) {
-        if (++spins > kSmallSpinLimit) {
+        if (++spins > s.spin_limit) {
             if (lane == 0) *s.failed = 1u;
             return false;
         }
@@ -114,7 +114,10 @@ __device__ __forceinline__ void small_finish(const SmallArgs &s, uint32_t wave, 
 // others leave at once.  An item waits until every item of the slices before
 // is done.  Tickets rise, and a block works on its tickets in order, so the
 // lowest unfinished item is always one that a running block works on: the
-// wait ends however many blocks run, one would do.
+// wait ends however many blocks run, one would do.  A wave whose wait passes its
+// limit tells the host (s.failed) and leaves; the others of its block end that
+// item, whose links are then wrong, and leave with the next ticket, and the blocks
+// that wait for its item give up in turn.
 //
 // A block is four waves.  Wave 0 updates; waves 1 and 2 make the forward and
 // the backward staples; wave 3 takes the next ticket once the staples have been
@@ -137,8 +140,9 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
 {
     using R = typename Store<PREC>::real;
     __shared__ LogEntry table[128];
-    // s_round: the item whose ticket has been taken; s_go: the item whose wait is over
-    __shared__ uint32_t s_ticket, s_round, s_go, s_mine;
+    // s_round: the item whose ticket has been taken; s_go: the item whose wait is
+    // over; s_quit: a wave gave up a wait and left
+    __shared__ uint32_t s_ticket, s_round, s_go, s_mine, s_quit;
     __shared__ Proposal s_proposal[2][64];
     __shared__ Direction<R> s_direction[2][64];
     __shared__ __align__(16) char s_lds[SplitLds<D, PREC>::kBytes];
@@ -154,6 +158,7 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
         if (s_mine) s_ticket = take();
         s_round = 1;
         s_go = 0;
+        s_quit = 0;
     }
     if (threadIdx.x < 128u) table[threadIdx.x] = kLogTable[threadIdx.x];
     __syncthreads();
@@ -164,7 +169,10 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
     for (uint32_t round = 1;; ++round) {
         uint32_t spins = 0;
         while (__hip_atomic_load(&s_round, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != round)
-            if (++spins > kSmallSpinLimit) return;
+            if (++spins > s.spin_limit * kSmallLdsPolls) {
+                if (lane == 0) *s.failed = s_quit = 1u;
+                return;
+            }
         const uint32_t t = __builtin_amdgcn_readfirstlane(s_ticket);
         if (t >= s.items) {
             // one block, with the first ticket past the end, adds up the
@@ -208,7 +216,8 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
             __syncthreads();
             __syncthreads();
             if (lane == 0) {
-                s_ticket = take();
+                const uint32_t next = take();
+                s_ticket = s_quit ? ~0u : next;
                 __hip_atomic_store(&s_round, round + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             continue;
@@ -218,13 +227,22 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
             s_direction[hit][lane] = draw_direction<R>(lid, sweep, split_word(hit), rep.key0, rep.key1);
         // every item of the slices before: wave 1 looks at the groups' words
         // (reads that pass the caches by: more of them would slow the links')
-        // and tells wave 2
+        // and tells wave 2 (also when it gives up: wave 2 need not wait longer)
         if (wave == 1) {
-            if (!small_wait(s, n, lane)) return;
+            if (!small_wait(s, n, lane)) {
+                if (lane == 0) {
+                    s_quit = 1u;
+                    __hip_atomic_store(&s_go, round, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                return;
+            }
             if (lane == 0) __hip_atomic_store(&s_go, round, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
             while (__hip_atomic_load(&s_go, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != round)
-                if (++spins > kSmallSpinLimit) return;
+                if (++spins > s.spin_limit * kSmallLdsPolls) {
+                    if (lane == 0) *s.failed = s_quit = 1u;
+                    return;
+                }
         }
         asm volatile("" ::: "memory");
         if (wave == 1) split_staples<D, PREC, true, kFresh>(a, rep, first, lds);
