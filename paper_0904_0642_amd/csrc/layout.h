@@ -172,13 +172,20 @@ struct UpdateArgs {
     uint32_t *barrier;           // persistent launches: kBarrierWords counters, zeroed before the launch
 };
 
-// Whole sweeps in one launch (small lattices): the next ticket, the XCD that
-// works (plus 1) and, for every group of 16 links, the slices it has done; cleared
-// before the launch.  Up to 64 groups an XCD gives each its block (two per
+// Whole sweeps in one launch (small lattices): the next ticket, the team of blocks
+// that works (small_team) and, for every group of 16 links, the slices it has done;
+// cleared before the launch.  Up to 64 groups an XCD gives each its block (two per
 // compute unit in FP64); with two rounds of blocks a slice takes longer than
 // launched by itself (2048 links, FP64-18: 9.9 us against 6.9 us).
 constexpr uint32_t kSmallGroups = 64;
-constexpr uint32_t kSmallTicket = 0, kSmallXcd = 32, kSmallDone = 64, kSmallWords = kSmallDone + kSmallGroups;
+constexpr uint32_t kSmallTicket = 0, kSmallTeam = 32, kSmallDone = 64, kSmallWords = kSmallDone + kSmallGroups;
+// The blocks of an XCD whose numbers leave the same remainder by 8: one block of a
+// grid of 8 per group for every group at most, also where the grid has fewer than
+// 8 XCDs (with 8, dealt round robin, all blocks of the XCD).  A block holds at most
+// one ticket whose wait is not over, so that no ticket is given out two slices
+// past an unfinished one, and a link may be loaded ahead of the wait: 2 D slices
+// lie between two writes of it.
+constexpr uint32_t small_team(uint32_t xcd, uint32_t block) { return (xcd << 3 | (block & 7u)) + 1u; }
 constexpr uint32_t kSmallQueues = 64;             // queues cleared together; each launch takes the next one
 // Polls until a wait for another block gives up, unless the host sets fewer.  A
 // wait for another wave of the block, which such a wait can hold up, polls LDS

@@ -150,11 +150,11 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
         return __hip_atomic_fetch_add(s.work + kSmallTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     if (threadIdx.x == 0) {
-        const uint32_t x = xcc_id();
+        const uint32_t team = small_team(xcc_id(), blockIdx.x);
         uint32_t old = 0;
-        __hip_atomic_compare_exchange_strong(s.work + kSmallXcd, &old, x + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+        __hip_atomic_compare_exchange_strong(s.work + kSmallTeam, &old, team, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
-        s_mine = old == 0u || old == x + 1u;
+        s_mine = old == 0u || old == team;
         if (s_mine) s_ticket = take();
         s_round = 1;
         s_go = 0;
@@ -190,7 +190,8 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
         const SplitSite<D> site(rep, first + (lane >> 2), a.parity);
         const uint32_t lid = split_lid<D>(rep, site, a.mu);
         if (wave == 0) {
-            // only this slice of the sweep before wrote this link
+            // only this slice of the sweep before wrote this link, and it is done
+            // without a wait (small_team)
             const LinkRef uptr = link_ref<D, PREC>(a.links, rep, site.layer, a.mu, a.parity, site.x.s);
             const mat3<R> U = load_link<PREC, kFresh>(uptr);
             __syncthreads();  // the staples and the draws are there
@@ -255,7 +256,7 @@ __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
 template <int D, int PREC>
 static hipError_t launch_small_t(hipStream_t st, const SmallArgs &s)
 {
-    // a block for every group on whichever XCD begins first
+    // a block for every group on whichever XCD begins first (small_team)
     const dim3 grid(8u * s.u.total_blocks), block(256);
     if (s.u.meas != nullptr && s.u.meas_classes == 3)
         hipLaunchKernelGGL((update_small_kernel<D, PREC, 3>), grid, block, 0, st, s);
