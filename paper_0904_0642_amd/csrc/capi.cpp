@@ -95,6 +95,7 @@ struct su3hb_lattice {
     } *host = nullptr;
     double *host_plaq = nullptr;  // 6 per replica
     bool stats_dirty = true;      // the slots hold counts that no call has read
+    bool words_stale = false;     // d_sweep holds what a call that failed left
     unsigned long long *d_maxdef = nullptr;
     double *d_stage = nullptr;
     void *ring = nullptr;         // pinned slots of large copies, from the first one on
@@ -670,6 +671,21 @@ int refuse_capture(const su3hb_lattice *L)
     return capture == hipStreamCaptureStatusNone ? SU3HB_OK : fail(SU3HB_EHIP, "the stream is being captured");
 }
 
+// Sweeps begin: the device's counter is the handle's and no partial sums wait,
+// unless a call failed between its launches.  The caller clears words_stale once
+// all launches that step the words, and those that add up the sums, are enqueued.
+int begin_sweeps(su3hb_lattice *L)
+{
+    if (L->words_stale) {
+        HIPCHK(launch_counter_set(L->stream, L->d_sweep, uint32_t(L->sweep)));
+        HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
+    }
+    L->words_stale = true;
+    return SU3HB_OK;
+}
+
+// Measured sweeps that are not small leave their sums to finish_measure, and
+// words_stale to its caller.
 int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measure, bool counters)
 {
     if (n <= 0) return SU3HB_OK;
@@ -677,6 +693,7 @@ int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int meas
     // a captured call could be replayed, with sweeps that this handle would not
     // count (su3hb_sweep_measure_static is the call for that)
     if (int rc = refuse_capture(L)) return rc;
+    if (int rc = begin_sweeps(L)) return rc;
     if (use_small(L)) {
         if (int rc = run_small(L, b0, b1, nhit, n, measure, counters)) return rc;
     } else {
@@ -686,6 +703,7 @@ int run_sweeps(su3hb_lattice *L, double b0, double b1, int nhit, int n, int meas
             if (int rc = enqueue_sweep(L, a)) return rc;
     }
     L->sweep += uint64_t(n);
+    L->words_stale = measure && !use_small(L);
     return SU3HB_OK;
 }
 
@@ -1122,6 +1140,7 @@ int su3hb_sweep_measure(su3hb_lattice *L, double beta0, double beta1, int n_hit,
         rc = run_sweeps(L, beta0, beta1, n_hit, chunk, 1, stats != nullptr);
         if (!rc && !use_small(L)) rc = finish_measure(L, beta0, beta1, chunk, L->host->series);
         if (rc) return rc;
+        L->words_stale = false;
         HIPCHK(hipStreamSynchronize(L->stream));
         std::memcpy(series + size_t(done) * 6, L->host->series, sizeof(double) * 6 * size_t(chunk));
         if ((rc = check_small(L)) != SU3HB_OK) return rc;
@@ -1182,8 +1201,11 @@ int su3hb_set_state(su3hb_lattice *L, uint64_t seed, uint64_t sweep)
     int rc = upload_reps(L);
     if (rc) return rc;
     L->sweep = sweep;
+    const bool stale = L->words_stale;
+    L->words_stale = true;
     HIPCHK(launch_counter_set(L->stream, L->d_sweep, uint32_t(sweep)));
     HIPCHK(hipStreamSynchronize(L->stream));
+    L->words_stale = stale;
     return SU3HB_OK;
 }
 
@@ -1234,6 +1256,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     } guard{backup};
     HIPCHK(hipMemcpyAsync(backup, L->links, L->links_bytes, hipMemcpyDeviceToDevice, L->stream));
     const uint64_t sweep0 = L->sweep;
+    L->words_stale = true;
     // candidate shapes: every block size and order, both occupancy targets for
     // D = 4; orders 2 to 6 only where they apply (otherwise they would repeat
     // another order), orders 3, 5 and 6 only with more than one wave per block
@@ -1339,6 +1362,7 @@ int su3hb_autotune(su3hb_lattice *L, int budget_ms)
     HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
     HIPCHK(hipStreamSynchronize(L->stream));
     L->sweep = sweep0;
+    L->words_stale = false;
     if (rc) return rc;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1372,6 +1396,7 @@ int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, i
     kinds.reserve(launches);
     UpdateArgs a;
     rc = sweep_args(L, beta0, beta1, n_hit, measure, false, &a);
+    if (!rc) rc = begin_sweeps(L);
     if (rc) return rc;
     for (int sw = 0; sw < n_sweeps; ++sw) {
         rc = enqueue_sweep(L, a, &kinds, &ev);
@@ -1384,6 +1409,7 @@ int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, i
         kinds.push_back(1);
     }
     L->sweep += uint64_t(n_sweeps);
+    L->words_stale = false;
     HIPCHK(hipStreamSynchronize(L->stream));
     double t_upd = 0, t_plq = 0, n_upd = 0, n_plq = 0;
     for (size_t i = 0; i < kinds.size(); ++i) {
@@ -1470,6 +1496,7 @@ int su3hb_batch_sweep(su3hb_batch *L, int n_hit, int n_sweeps, int mode, su3hb_s
         // one resident block per CU (as many as fit), slices separated by a
         // grid barrier; a barrier that gives up raises a flag checked below
         if (int rc2 = check_sweep_room(L, n_sweeps)) return rc2;
+        if (int rc2 = begin_sweeps(L)) return rc2;
         int per_cu = 0;
         HIPCHK(persistent_max_blocks(L->nd, L->prec, &per_cu));
         if (per_cu < 1) return fail(SU3HB_EUNSUPPORTED, "persistent kernel cannot be resident");
@@ -1489,6 +1516,7 @@ int su3hb_batch_sweep(su3hb_batch *L, int n_hit, int n_sweeps, int mode, su3hb_s
             done += n;
         }
         L->sweep += uint64_t(n_sweeps);
+        L->words_stale = false;
         uint32_t flag = 0;
         HIPCHK(hipMemcpyAsync(&flag, L->d_bar + kBarrierFlag, sizeof flag, hipMemcpyDeviceToHost, L->stream));
         HIPCHK(hipStreamSynchronize(L->stream));

@@ -1,0 +1,284 @@
+// The C ABI (capi.cpp) built for the host over a stand-in for the HIP runtime and
+// the kernels' launchers, all of whose calls end at once and any of which can be
+// made to fail.  The launchers do what the kernels do to what capi.cpp keeps between
+// calls: the sweep counter's words, the partial sums' places, the queues of launches
+// that hold whole sweeps.  Usage: capi_host <scenario>; prints what went wrong
+// and exits with 1, or nothing and 0.
+#include <hip/hip_runtime.h>
+
+#include <cstdarg>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "kernels.h"
+#include "su3hb.h"
+
+using namespace su3hb;
+
+namespace {
+
+int g_bad = 0;
+std::map<char *, size_t> g_memory;   // device allocations
+int g_fail_in = -1;                  // launches until one fails; -1: none
+uint32_t g_swept = 0;                // last sweep index that a slice drew with
+uint32_t g_slices = 0;               // slices done
+
+void bad(const char *fmt, ...)
+{
+    va_list ap;
+    va_start(ap, fmt);
+    vprintf(fmt, ap);
+    va_end(ap);
+    printf("\n");
+    ++g_bad;
+}
+
+#define EXPECT(cond)                                                        \
+    do {                                                                    \
+        if (!(cond)) bad("line %d: not %s (%s)", __LINE__, #cond, su3hb_last_error()); \
+    } while (0)
+
+hipError_t launch() { return g_fail_in >= 0 && g_fail_in-- == 0 ? hipErrorUnknown : hipSuccess; }
+
+bool in_memory(const void *p, size_t bytes)
+{
+    for (auto &m : g_memory)
+        if (static_cast<const char *>(p) >= m.first && static_cast<const char *>(p) + bytes <= m.first + m.second)
+            return true;
+    return false;
+}
+
+// what a slice kernel does besides its links
+hipError_t slice(int D, const UpdateArgs &a)
+{
+    if (hipError_t e = launch()) return e;
+    const uint32_t sweep = a.sweep[a.parity];
+    g_swept = sweep;
+    ++g_slices;
+    if (a.meas != nullptr && a.parity == 1) {
+        double *m = a.meas + (size_t(a.sweep[3]) * D + a.mu) * a.total_blocks * a.meas_classes;
+        const size_t n = size_t(a.total_blocks) * a.meas_classes;
+        if (!in_memory(m, n * sizeof(double))) bad("partial sums of place %u outside their buffer", a.sweep[3]);
+        else
+            for (size_t i = 0; i < n; ++i) m[i] = sweep;
+    }
+    if (a.mu == D - 1) {  // advance_sweep
+        a.sweep[1 - a.parity] = sweep + uint32_t(a.parity);
+        if (a.meas != nullptr) a.sweep[3 - a.parity] = a.sweep[2 + a.parity] + uint32_t(a.parity);
+    }
+    return hipSuccess;
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// the runtime
+
+extern "C" {
+
+void **__hipRegisterFatBinary(const void *) { return nullptr; }
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipUnregisterFatBinary(void **) {}
+
+hipError_t hipMalloc(void **p, size_t n)
+{
+    *p = std::calloc(n, 1);
+    g_memory[static_cast<char *>(*p)] = n;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    g_memory.erase(static_cast<char *>(p));
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return (*p = std::calloc(n, 1)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "an error"; }
+hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorInvalidSymbol; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *)
+{
+    at->type = hipMemoryTypeUnregistered;
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = reinterpret_cast<hipEvent_t>(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+
+}  // extern "C"
+
+// ---------------------------------------------------------------------------
+// the launchers
+
+namespace su3hb {
+
+hipError_t launch_update(int D, int, int, dim3, dim3, hipStream_t, const UpdateArgs &a) { return slice(D, a); }
+hipError_t launch_update_split(int D, int, hipStream_t, const UpdateArgs &a) { return slice(D, a); }
+hipError_t launch_update_planes(int D, int, hipStream_t, const UpdateArgs &a) { return slice(D, a); }
+hipError_t launch_update_small(int D, int, hipStream_t, const SmallArgs &s)
+{
+    if (hipError_t e = launch()) return e;
+    if (s.work[kSmallTicket] != 0) {
+        bad("a queue that is not empty");
+        return hipSuccess;
+    }
+    s.work[kSmallTicket] = s.items + 1;
+    g_swept = s.sweep0 + s.sweeps - 1;
+    g_slices += 2u * uint32_t(D) * s.sweeps;
+    s.u.sweep[0] = s.sweep0 + s.sweeps;
+    if (s.u.meas)
+        for (uint32_t i = 0; i < s.sweeps; ++i) s.series[6 * i] = s.sweep0 + i;
+    return hipSuccess;
+}
+hipError_t launch_update_persistent(int, int, int, hipStream_t, const UpdateArgs &a, int n)
+{
+    if (hipError_t e = launch()) return e;
+    g_swept = a.sweep[0] + uint32_t(n) - 1;
+    return hipSuccess;
+}
+hipError_t persistent_max_blocks(int, int, int *n) { *n = 2; return hipSuccess; }
+hipError_t update_lds(int, int, int, dim3, const UpdateArgs &, size_t *need, size_t *limit)
+{
+    *need = 0;
+    *limit = 1;
+    return hipSuccess;
+}
+hipError_t launch_plaquette(int, int, dim3, dim3, hipStream_t, const PlaqArgs &) { return launch(); }
+hipError_t launch_plaquette_finalize(hipStream_t, const RepDesc *, int, int, const double *, double *) { return launch(); }
+hipError_t launch_measure_finalize(hipStream_t, const double *meas, int n, int D, uint32_t nblocks, int nc, double, int,
+                                   double, double, double *series, uint32_t *sweep)
+{
+    if (hipError_t e = launch()) return e;
+    if (sweep[2] != uint32_t(n)) bad("%u measured sweeps wait, %d are added up", sweep[2], n);
+    for (int i = 0; i < n; ++i) series[6 * i] = meas[(size_t(i) * D + 1) * nblocks * nc];
+    sweep[2] = 0;
+    return hipSuccess;
+}
+hipError_t launch_start(int, int, hipStream_t, void *, const RepDesc *, int, uint32_t, int) { return launch(); }
+hipError_t launch_pack(int, int, hipStream_t, const void *, const RepDesc *, int, uint64_t, uint32_t, double *) { return launch(); }
+hipError_t launch_unpack(int, int, hipStream_t, void *, const RepDesc *, int, uint64_t, uint32_t, const double *) { return launch(); }
+hipError_t launch_validate(hipStream_t, const double *, uint64_t, unsigned long long *) { return launch(); }
+hipError_t launch_rep_set(hipStream_t, const RepDesc &r, RepDesc *d) { *d = r; return launch(); }
+hipError_t launch_stats_zero(hipStream_t, StatSlot *) { return launch(); }
+hipError_t launch_stats_reduce(hipStream_t, StatSlot *, StatSlot *) { return launch(); }
+hipError_t launch_counter_add(hipStream_t, uint32_t *c, uint32_t n) { if (hipError_t e = launch()) return e; *c += n; return hipSuccess; }
+hipError_t launch_counter_set(hipStream_t, uint32_t *c, uint32_t v) { if (hipError_t e = launch()) return e; *c = v; return hipSuccess; }
+hipError_t launch_measure_begin(hipStream_t, uint32_t *s) { if (hipError_t e = launch()) return e; s[2] = 0; return hipSuccess; }
+hipError_t launch_u32_zero(hipStream_t, uint32_t *p, int n)
+{
+    if (hipError_t e = launch()) return e;
+    for (int i = 0; i < n; ++i) p[i] = 0;
+    return hipSuccess;
+}
+hipError_t launch_u64_zero(hipStream_t, unsigned long long *p, int n)
+{
+    if (hipError_t e = launch()) return e;
+    for (int i = 0; i < n; ++i) p[i] = 0;
+    return hipSuccess;
+}
+
+}  // namespace su3hb
+
+// ---------------------------------------------------------------------------
+
+namespace {
+
+su3hb_lattice *lattice(std::vector<int> ext)
+{
+    su3hb_params p{};
+    p.nd = int(ext.size());
+    for (size_t i = 0; i < ext.size(); ++i) p.extents[i] = ext[i];
+    p.nlat = 1;
+    p.start = SU3HB_COLD;
+    p.seed = 1;
+    su3hb_lattice *L = nullptr;
+    if (su3hb_init_lattice(&L, &p) != SU3HB_OK) {
+        bad("no lattice: %s", su3hb_last_error());
+        std::exit(1);
+    }
+    return L;
+}
+
+uint64_t sweep_of(const su3hb_lattice *L)
+{
+    uint64_t n = 0;
+    su3hb_get_state(L, nullptr, &n);
+    return n;
+}
+
+// A call of 3 measured sweeps fails at its k-th launch, for every k; the next call,
+// which fills the room of the partial sums, keeps to it, gives its own rows and
+// draws with the sweep indices that the handle counts.
+void failed_measurement()
+{
+    for (const std::vector<int> &ext : {std::vector<int>{4, 4}, {12, 8, 8, 6}, {16, 16, 16, 16}, {24, 24, 24, 16}})
+        for (int timed = 0; timed < 2; ++timed)
+            for (int k = 0;; ++k) {
+                su3hb_lattice *L = lattice(ext);
+                double series[6 * 16] = {}, timing[4];
+                EXPECT(su3hb_sweep(L, 6, 6, 8, 2, nullptr) == SU3HB_OK);
+                g_fail_in = k;
+                const int rc = timed ? su3hb_sweep_timed(L, 6, 6, 8, 3, 1, series, timing)
+                                     : su3hb_sweep_measure(L, 6, 6, 8, 3, series, nullptr);
+                const bool failed = g_fail_in < 0;
+                g_fail_in = -1;
+                EXPECT(rc == (failed ? SU3HB_EHIP : SU3HB_OK));
+                const uint64_t at = sweep_of(L);
+                EXPECT(su3hb_sweep_measure(L, 6, 6, 8, 16, series, nullptr) == SU3HB_OK);
+                for (int i = 0; i < 16; ++i) EXPECT(series[6 * i] == double(at + uint64_t(i)));
+                EXPECT(g_swept == at + 15 && sweep_of(L) == at + 16);
+                su3hb_free(L);
+                if (!failed) break;
+            }
+}
+
+// A call of unmeasured sweeps that fails between its launches leaves the sweep
+// indices of later ones as the handle counts them.
+void failed_sweeps()
+{
+    for (const std::vector<int> &ext : {std::vector<int>{4, 4}, {12, 8, 8, 6}, {24, 24, 24, 16}})
+        for (int k = 0;; ++k) {
+            su3hb_lattice *L = lattice(ext);
+            EXPECT(su3hb_sweep(L, 6, 6, 8, 2, nullptr) == SU3HB_OK);
+            g_fail_in = k;
+            su3hb_stats st;
+            const int rc = su3hb_sweep(L, 6, 6, 8, 3, k % 2 ? &st : nullptr);
+            const bool failed = g_fail_in < 0;
+            g_fail_in = -1;
+            EXPECT(rc == (failed ? SU3HB_EHIP : SU3HB_OK));
+            const uint64_t at = sweep_of(L);
+            EXPECT(su3hb_sweep(L, 6, 6, 8, 1, nullptr) == SU3HB_OK);
+            EXPECT(g_swept == at);
+            su3hb_free(L);
+            if (!failed) break;
+        }
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::map<std::string, void (*)()> scenarios = {
+        {"failed_measurement", failed_measurement},
+        {"failed_sweeps", failed_sweeps},
+    };
+    const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
+    if (it == scenarios.end()) return 2;
+    it->second();
+    return g_bad ? 1 : 0;
+}
