@@ -209,8 +209,9 @@ int su3hb_set_state(su3hb_lattice *lat, uint64_t seed, uint64_t sweep);
  * slices hold few links (from 20480 to 49152 by dimension and precision) share
  * every link's update between lanes or waves, and calls on those of at most 1024 links per slice run all their
  * sweeps in one launch (in blocks of one XCD that wait for each other's
- * slices; a wait past its limit ends the launch, and the next call that
- * synchronises returns SU3HB_EHIP).  The shape then stands for nothing.
+ * slices; a wait past its limit ends the launch, and the calls that synchronise,
+ * but set_state, return SU3HB_EHIP until set_links has replaced the links, of a
+ * batch those of every replica).  The shape then stands for nothing.
  * A shape whose LDS (staple snapshots of a measured slice plus staging
  * areas) exceeds the device's per-block limit returns SU3HB_EUNSUPPORTED
  * and leaves the launch shape as it was. */

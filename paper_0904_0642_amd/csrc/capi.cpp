@@ -109,6 +109,7 @@ struct su3hb_lattice {
     uint32_t *d_work = nullptr;   // queues of launches that hold whole sweeps
     uint32_t small_launches = 0;  // such launches so far
     uint32_t wait_limit = kSmallSpinLimit;  // polls of a wait in them
+    std::vector<char> swept;      // per replica: sweeps since its links were set
     uint32_t upd_blocks = 0, plq_blocks = 0, pers_blocks = 0;
     std::vector<hipEvent_t> events;
     int num_cus = 0;
@@ -246,6 +247,7 @@ int alloc_common(su3hb_lattice *L)
     HIPCHK(hipDeviceGetAttribute(&L->num_cus, hipDeviceAttributeMultiprocessorCount, L->device));
     HIPCHK(hipHostMalloc(&L->host, sizeof(*L->host) + sizeof(double) * 6 * L->reps.size(), 0));
     L->host->failed = 0;
+    L->swept.assign(L->reps.size(), 0);
     L->host_plaq = reinterpret_cast<double *>(L->host + 1);
     layout_reps(L);
     // the device's tables and accumulators: one allocation, places of 256 bytes
@@ -656,11 +658,24 @@ int run_small(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measu
 }
 
 // After a synchronisation: whether a launch of whole sweeps gave up a wait.
+bool small_failed(const su3hb_lattice *L) { return *static_cast<volatile uint32_t *>(&L->host->failed) != 0; }
+
 int check_small(const su3hb_lattice *L)
 {
-    if (*static_cast<volatile uint32_t *>(&L->host->failed))
+    if (small_failed(L))
         return fail(SU3HB_EHIP, "a sweep waited past its limit; the links are not valid");
     return SU3HB_OK;
+}
+
+// Replica r's links have been replaced, and nothing runs.  What a launch that gave
+// up a wait did is gone once all have been, but for the sweep counter, which it
+// may not have stepped.
+void links_replaced(su3hb_lattice *L, int r)
+{
+    L->swept[size_t(r)] = 0;
+    if (!small_failed(L) || std::count(L->swept.begin(), L->swept.end(), 1)) return;
+    L->host->failed = 0;
+    L->words_stale = true;
 }
 
 // The null stream cannot be captured.
@@ -681,6 +696,7 @@ int begin_sweeps(su3hb_lattice *L)
         HIPCHK(launch_measure_begin(L->stream, L->d_sweep));
     }
     L->words_stale = true;
+    std::fill(L->swept.begin(), L->swept.end(), 1);
     return SU3HB_OK;
 }
 
@@ -918,6 +934,7 @@ int set_replica_links(su3hb_lattice *L, int r, const double *host, size_t n)
         HIPCHK(launch_unpack(L->nd, L->prec, L->stream, L->links, L->d_reps, r, c0, cnt, L->d_stage));
         HIPCHK(hipStreamSynchronize(L->stream));
     }
+    links_replaced(L, r);
     return SU3HB_OK;
 }
 
@@ -942,6 +959,7 @@ int apply_launch(su3hb_lattice *L, int block, int order, int waves)
     if (waves != 2 && !(waves == 3 && L->nd == 4) && !(waves == 4 && L->nd == 4 && is_fp32(L->prec)))
         return fail(SU3HB_EINVAL, "waves = %d: 2, or 3 for D = 4, or 4 for D = 4 with FP32 links", waves);
     HIPCHK(hipStreamSynchronize(L->stream));
+    if (int rc = check_small(L)) return rc;
     const bool old_set = L->shape_set;
     const int old_block = L->block, old_order = L->order, old_waves = L->waves;
     L->block = block;
@@ -1430,7 +1448,7 @@ int su3hb_sweep_timed(su3hb_lattice *L, double beta0, double beta1, int n_hit, i
     if (measure && n_sweeps > 0) {
         std::memcpy(series, L->host->series, sizeof(double) * 6 * size_t(n_sweeps));
     }
-    return SU3HB_OK;
+    return check_small(L);
 }
 
 // ---------------------------------------------------------------------------
@@ -1521,6 +1539,7 @@ int su3hb_batch_sweep(su3hb_batch *L, int n_hit, int n_sweeps, int mode, su3hb_s
         HIPCHK(hipMemcpyAsync(&flag, L->d_bar + kBarrierFlag, sizeof flag, hipMemcpyDeviceToHost, L->stream));
         HIPCHK(hipStreamSynchronize(L->stream));
         if (flag) return fail(SU3HB_EHIP, "persistent sweep: a grid barrier timed out; the links are not valid");
+        if ((rc = check_small(L)) != SU3HB_OK) return rc;
     }
     if (stats) return read_stats(L, stats);
     return SU3HB_OK;

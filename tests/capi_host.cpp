@@ -26,6 +26,7 @@ std::map<char *, size_t> g_memory;   // device allocations
 int g_fail_in = -1;                  // launches until one fails; -1: none
 uint32_t g_swept = 0;                // last sweep index that a slice drew with
 uint32_t g_slices = 0;               // slices done
+bool g_give_up = false;              // launches of whole sweeps give up a wait
 
 void bad(const char *fmt, ...)
 {
@@ -138,6 +139,10 @@ hipError_t launch_update_small(int D, int, hipStream_t, const SmallArgs &s)
         return hipSuccess;
     }
     s.work[kSmallTicket] = s.items + 1;
+    if (g_give_up) {
+        *s.failed = 1;
+        return hipSuccess;
+    }
     g_swept = s.sweep0 + s.sweeps - 1;
     g_slices += 2u * uint32_t(D) * s.sweeps;
     s.u.sweep[0] = s.sweep0 + s.sweeps;
@@ -269,6 +274,86 @@ void failed_sweeps()
         }
 }
 
+// A launch of whole sweeps gives up a wait.  Every call that synchronises says so,
+// until set_links has replaced the links (of every replica); then all is as the
+// handle counts it.
+void given_up_waits()
+{
+    std::vector<double> links;
+    double series[6 * 4], out[6], timing[4];
+    su3hb_stats st;
+    using Call = int (*)(su3hb_lattice *, double *, double *, double *, su3hb_stats *, std::vector<double> &);
+    const Call calls[] = {
+        [](su3hb_lattice *L, double *, double *o, double *, su3hb_stats *, std::vector<double> &) { return su3hb_plaquette(L, 6, 6, o); },
+        [](su3hb_lattice *L, double *, double *, double *, su3hb_stats *, std::vector<double> &l) { return su3hb_get_links(L, l.data(), l.size()); },
+        [](su3hb_lattice *L, double *, double *, double *, su3hb_stats *s, std::vector<double> &) { return su3hb_sweep(L, 6, 6, 8, 1, s); },
+        [](su3hb_lattice *L, double *, double *, double *, su3hb_stats *s, std::vector<double> &) { return su3hb_overrelax(L, 6, 6, 1, s); },
+        [](su3hb_lattice *L, double *s, double *, double *, su3hb_stats *, std::vector<double> &) { return su3hb_sweep_measure(L, 6, 6, 8, 4, s, nullptr); },
+        [](su3hb_lattice *L, double *s, double *, double *t, su3hb_stats *, std::vector<double> &) { return su3hb_sweep_timed(L, 6, 6, 8, 2, 1, s, t); },
+        [](su3hb_lattice *L, double *, double *, double *, su3hb_stats *, std::vector<double> &) { return su3hb_set_launch(L, 256, 1, 2); },
+        [](su3hb_lattice *L, double *, double *, double *, su3hb_stats *, std::vector<double> &) { return su3hb_autotune(L, 1); },
+    };
+    for (size_t c = 0; c < sizeof calls / sizeof *calls; ++c) {
+        const int n1 = 4 + 2 * int(c);  // shapes that nothing has tuned
+        su3hb_lattice *L = lattice({4, n1});
+        links.assign(size_t(4 * n1 * 2 * 18), 0.0);
+        g_give_up = true;
+        EXPECT(su3hb_sweep(L, 6, 6, 8, 3, nullptr) == SU3HB_OK);
+        g_give_up = false;
+        for (int twice = 0; twice < 2; ++twice) {
+            const int rc = calls[c](L, series, out, timing, &st, links);
+            if (rc != SU3HB_EHIP) bad("call %zu returns %d", c, rc);
+        }
+        EXPECT(su3hb_set_state(L, 1, 7) == SU3HB_OK);
+        EXPECT(su3hb_plaquette(L, 6, 6, out) == SU3HB_EHIP);
+        EXPECT(su3hb_set_links(L, links.data(), links.size()) == SU3HB_OK);
+        for (size_t k = 0; k < sizeof calls / sizeof *calls; ++k) {
+            const int rc = calls[k](L, series, out, timing, &st, links);
+            if (rc != SU3HB_OK) bad("after set_links call %zu returns %d (%s)", k, rc, su3hb_last_error());
+        }
+        const uint64_t at = sweep_of(L);
+        EXPECT(at == 7 + 1 + 1 + 4 + 2);
+        EXPECT(su3hb_sweep_timed(L, 6, 6, 8, 1, 0, nullptr, timing) == SU3HB_OK && g_swept == at);
+        su3hb_free(L);
+    }
+    // the sweep index of a launch that did not step the device's
+    su3hb_lattice *L = lattice({4, 40});
+    links.assign(4 * 40 * 2 * 18, 0.0);
+    g_give_up = true;
+    EXPECT(su3hb_sweep(L, 6, 6, 8, 3, nullptr) == SU3HB_OK);
+    g_give_up = false;
+    EXPECT(su3hb_set_links(L, links.data(), links.size()) == SU3HB_OK);
+    EXPECT(su3hb_sweep_timed(L, 6, 6, 8, 1, 0, nullptr, timing) == SU3HB_OK);
+    EXPECT(g_swept == 3 && sweep_of(L) == 4);
+    su3hb_free(L);
+
+    su3hb_replica_desc reps[3] = {};
+    for (auto &r : reps) {
+        r.extents[0] = r.extents[1] = 4;
+        r.beta = 6;
+        r.start = SU3HB_COLD;
+    }
+    su3hb_batch *B = nullptr;
+    EXPECT(su3hb_batch_create(&B, 2, reps, 3, SU3HB_FP64_18, nullptr) == SU3HB_OK);
+    std::vector<double> rows(18);
+    const size_t n = 4 * 4 * 2 * 18;
+    g_give_up = true;
+    EXPECT(su3hb_batch_sweep(B, 8, 2, 0, nullptr) == SU3HB_OK);
+    g_give_up = false;
+    EXPECT(su3hb_batch_sweep(B, 8, 1, 1, nullptr) == SU3HB_EHIP);
+    EXPECT(su3hb_batch_plaquette(B, rows.data(), rows.size()) == SU3HB_EHIP);
+    EXPECT(su3hb_batch_get_links(B, 1, links.data(), n) == SU3HB_EHIP);
+    for (int r : {0, 1}) EXPECT(su3hb_batch_set_links(B, r, links.data(), n) == SU3HB_OK);
+    EXPECT(su3hb_batch_sweep(B, 8, 1, 0, nullptr) == SU3HB_OK);  // all replicas in doubt again
+    for (int r : {2, 0, 1}) {
+        EXPECT(su3hb_batch_plaquette(B, rows.data(), rows.size()) == SU3HB_EHIP);
+        EXPECT(su3hb_batch_set_links(B, r, links.data(), n) == SU3HB_OK);
+    }
+    EXPECT(su3hb_batch_plaquette(B, rows.data(), rows.size()) == SU3HB_OK);
+    EXPECT(su3hb_batch_sweep(B, 8, 1, 1, nullptr) == SU3HB_OK);
+    su3hb_batch_free(B);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -276,6 +361,7 @@ int main(int argc, char **argv)
     const std::map<std::string, void (*)()> scenarios = {
         {"failed_measurement", failed_measurement},
         {"failed_sweeps", failed_sweeps},
+        {"given_up_waits", given_up_waits},
     };
     const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
     if (it == scenarios.end()) return 2;
