@@ -647,9 +647,11 @@ int run_small(su3hb_lattice *L, double b0, double b1, int nhit, int n, int measu
         s.items = per_sweep * uint32_t(k);
         s.sweep0 = uint32_t(L->sweep + uint64_t(done));
         s.sweeps = uint32_t(k);
-        // a queue of its own for every launch; all are cleared once in a round
-        const uint32_t queue = L->small_launches++ % kSmallQueues;
+        // a queue of its own for every launch; all are cleared once in a round, and
+        // a clearing that fails is made up for by the next call
+        const uint32_t queue = L->small_launches % kSmallQueues;
         if (queue == 0) HIPCHK(launch_u32_zero(L->stream, L->d_work, int(kSmallWords * kSmallQueues)));
+        ++L->small_launches;
         s.work = L->d_work + queue * kSmallWords;
         HIPCHK(launch_update_small(L->nd, L->prec, L->stream, s));
         done += k;

@@ -135,7 +135,7 @@ hipError_t launch_update_small(int D, int, hipStream_t, const SmallArgs &s)
 {
     if (hipError_t e = launch()) return e;
     if (s.work[kSmallTicket] != 0) {
-        bad("a queue that is not empty");
+        bad("a queue that is not empty: no sweep is done");
         return hipSuccess;
     }
     s.work[kSmallTicket] = s.items + 1;
@@ -354,6 +354,25 @@ void given_up_waits()
     su3hb_batch_free(B);
 }
 
+// More calls than there are queues, of which one fails at its first, second or
+// third launch: no later one gets a queue that has been used.
+void failed_clearing()
+{
+    for (int k = 0; k < 3; ++k)
+        for (uint32_t nth : {0u, 1u, kSmallQueues - 1, kSmallQueues, kSmallQueues + 1}) {
+            su3hb_lattice *L = lattice({4, 4});
+            for (uint32_t i = 0; i < 3 * kSmallQueues; ++i) {
+                if (i == nth || i == nth + kSmallQueues) g_fail_in = k;
+                const int rc = su3hb_sweep(L, 6, 6, 8, 1, nullptr);
+                const bool failed = (i == nth || i == nth + kSmallQueues) && g_fail_in < 0;
+                g_fail_in = -1;
+                EXPECT(rc == (failed ? SU3HB_EHIP : SU3HB_OK));
+                if (rc == SU3HB_OK) EXPECT(g_swept + 1 == sweep_of(L));
+            }
+            su3hb_free(L);
+        }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -362,6 +381,7 @@ int main(int argc, char **argv)
         {"failed_measurement", failed_measurement},
         {"failed_sweeps", failed_sweeps},
         {"given_up_waits", given_up_waits},
+        {"failed_clearing", failed_clearing},
     };
     const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
     if (it == scenarios.end()) return 2;
