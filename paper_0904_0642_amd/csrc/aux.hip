@@ -248,9 +248,8 @@ hipError_t launch_measure_finalize(hipStream_t st, const double *meas, int n, in
                                    double V, int nlat, double beta0, double beta1, double *series, uint32_t *sweep)
 {
     if (nc != 1 && nc != 3) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(measure_finalize_kernel, dim3(n), dim3(1024), 0, st, meas, D, nblocks, nc, V, nlat, beta0,
-                       beta1, series, sweep);
-    return hipGetLastError();
+    return launch_kernel(measure_finalize_kernel, dim3(n), dim3(1024), st, meas, D, nblocks, nc, V, nlat, beta0,
+                         beta1, series, sweep);
 }
 
 // One block per replica: fixed-order sum of its block partials, normalised.
@@ -283,9 +282,8 @@ __global__ void __launch_bounds__(256) plaquette_finalize_kernel(const RepDesc *
 template <int D, int PREC>
 static hipError_t launch_plaquette_t(dim3 g, dim3 b, hipStream_t st, const PlaqArgs &a)
 {
-    if (a.by_site) hipLaunchKernelGGL((plaquette_site_kernel<D, PREC>), dim3((g.x + 7) / 8 * 8), b, 0, st, a);
-    else hipLaunchKernelGGL((plaquette_kernel<D, PREC>), g, b, 0, st, a);
-    return hipGetLastError();
+    if (a.by_site) return launch_kernel(plaquette_site_kernel<D, PREC>, dim3((g.x + 7) / 8 * 8), b, st, a);
+    return launch_kernel(plaquette_kernel<D, PREC>, g, b, st, a);
 }
 
 hipError_t launch_plaquette(int D, int prec, dim3 g, dim3 b, hipStream_t st, const PlaqArgs &a)
@@ -313,8 +311,7 @@ hipError_t launch_plaquette(int D, int prec, dim3 g, dim3 b, hipStream_t st, con
 hipError_t launch_plaquette_finalize(hipStream_t st, const RepDesc *reps, int nrep, int D,
                                      const double *partials, double *out)
 {
-    hipLaunchKernelGGL(plaquette_finalize_kernel, dim3(nrep), dim3(256), 0, st, reps, D, partials, out);
-    return hipGetLastError();
+    return launch_kernel(plaquette_finalize_kernel, dim3(nrep), dim3(256), st, reps, D, partials, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -448,21 +445,19 @@ __global__ void __launch_bounds__(256) unpack_kernel(void *links, const RepDesc 
     }
 #define SU3HB_PREC(KERNEL, DD, ...)                                                        \
     switch (prec) {                                                                        \
-    case kFP64_18: hipLaunchKernelGGL((KERNEL<DD, kFP64_18>), __VA_ARGS__); break;         \
-    case kFP32_18: hipLaunchKernelGGL((KERNEL<DD, kFP32_18>), __VA_ARGS__); break;         \
-    case kFP32_12: hipLaunchKernelGGL((KERNEL<DD, kFP32_12>), __VA_ARGS__); break;         \
-    case kFP64_12: hipLaunchKernelGGL((KERNEL<DD, kFP64_12>), __VA_ARGS__); break;         \
+    case kFP64_18: return launch_kernel(KERNEL<DD, kFP64_18>, __VA_ARGS__);                \
+    case kFP32_18: return launch_kernel(KERNEL<DD, kFP32_18>, __VA_ARGS__);                \
+    case kFP32_12: return launch_kernel(KERNEL<DD, kFP32_12>, __VA_ARGS__);                \
+    case kFP64_12: return launch_kernel(KERNEL<DD, kFP64_12>, __VA_ARGS__);                \
     default: return hipErrorInvalidValue;                                                  \
-    }                                                                                      \
-    break;
+    }
 
 hipError_t launch_start(int D, int prec, hipStream_t st, void *links, const RepDesc *reps, int r,
                         uint32_t nthreads, int mode)
 {
     if (nthreads == 0) return hipSuccess;
     const dim3 g((nthreads + 255) / 256), b(256);
-    SU3HB_DISPATCH(start_kernel, g, b, 0, st, links, reps, r, nthreads, mode)
-    return hipGetLastError();
+    SU3HB_DISPATCH(start_kernel, g, b, st, links, reps, r, nthreads, mode)
 }
 
 hipError_t launch_pack(int D, int prec, hipStream_t st, const void *links, const RepDesc *reps, int r,
@@ -470,8 +465,7 @@ hipError_t launch_pack(int D, int prec, hipStream_t st, const void *links, const
 {
     if (count == 0) return hipSuccess;
     const dim3 g((count + 255) / 256), b(256);
-    SU3HB_DISPATCH(pack_kernel, g, b, 0, st, links, reps, r, c0, count, dst)
-    return hipGetLastError();
+    SU3HB_DISPATCH(pack_kernel, g, b, st, links, reps, r, c0, count, dst)
 }
 
 hipError_t launch_unpack(int D, int prec, hipStream_t st, void *links, const RepDesc *reps, int r,
@@ -479,8 +473,7 @@ hipError_t launch_unpack(int D, int prec, hipStream_t st, void *links, const Rep
 {
     if (count == 0) return hipSuccess;
     const dim3 g((count + 255) / 256), b(256);
-    SU3HB_DISPATCH(unpack_kernel, g, b, 0, st, links, reps, r, c0, count, src)
-    return hipGetLastError();
+    SU3HB_DISPATCH(unpack_kernel, g, b, st, links, reps, r, c0, count, src)
 }
 
 // ---------------------------------------------------------------------------
@@ -534,9 +527,8 @@ __global__ void __launch_bounds__(256) validate_kernel(const double *src, uint64
 hipError_t launch_validate(hipStream_t st, const double *src, uint64_t nmat, unsigned long long *maxdef)
 {
     if (nmat == 0) return hipSuccess;
-    hipLaunchKernelGGL(validate_kernel, dim3(uint32_t((nmat + 255) / 256)), dim3(256), 0, st, src, nmat,
-                       maxdef);
-    return hipGetLastError();
+    return launch_kernel(validate_kernel, dim3(uint32_t((nmat + 255) / 256)), dim3(256), st, src, nmat,
+                         maxdef);
 }
 
 // ---------------------------------------------------------------------------
@@ -619,50 +611,42 @@ __global__ void rep_set_kernel(RepDesc r, RepDesc *dst)
 
 hipError_t launch_rep_set(hipStream_t st, const RepDesc &r, RepDesc *dst)
 {
-    hipLaunchKernelGGL(rep_set_kernel, dim3(1), dim3(64), 0, st, r, dst);
-    return hipGetLastError();
+    return launch_kernel(rep_set_kernel, dim3(1), dim3(64), st, r, dst);
 }
 
 hipError_t launch_stats_zero(hipStream_t st, StatSlot *slots)
 {
-    hipLaunchKernelGGL(stats_zero_kernel, dim3(1), dim3(kStatSlots), 0, st, slots);
-    return hipGetLastError();
+    return launch_kernel(stats_zero_kernel, dim3(1), dim3(kStatSlots), st, slots);
 }
 
 hipError_t launch_stats_reduce(hipStream_t st, StatSlot *slots, StatSlot *out)
 {
-    hipLaunchKernelGGL(stats_reduce_kernel, dim3(1), dim3(kStatSlots), 0, st, slots, out);
-    return hipGetLastError();
+    return launch_kernel(stats_reduce_kernel, dim3(1), dim3(kStatSlots), st, slots, out);
 }
 
 hipError_t launch_counter_add(hipStream_t st, uint32_t *ctr, uint32_t add)
 {
-    hipLaunchKernelGGL(counter_add_kernel, dim3(1), dim3(64), 0, st, ctr, add);
-    return hipGetLastError();
+    return launch_kernel(counter_add_kernel, dim3(1), dim3(64), st, ctr, add);
 }
 
 hipError_t launch_counter_set(hipStream_t st, uint32_t *ctr, uint32_t value)
 {
-    hipLaunchKernelGGL(counter_set_kernel, dim3(1), dim3(64), 0, st, ctr, value);
-    return hipGetLastError();
+    return launch_kernel(counter_set_kernel, dim3(1), dim3(64), st, ctr, value);
 }
 
 hipError_t launch_measure_begin(hipStream_t st, uint32_t *sweep)
 {
-    hipLaunchKernelGGL(measure_begin_kernel, dim3(1), dim3(64), 0, st, sweep);
-    return hipGetLastError();
+    return launch_kernel(measure_begin_kernel, dim3(1), dim3(64), st, sweep);
 }
 
 hipError_t launch_u32_zero(hipStream_t st, uint32_t *p, int n)
 {
-    hipLaunchKernelGGL(u32_zero_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n);
-    return hipGetLastError();
+    return launch_kernel(u32_zero_kernel, dim3((n + 255) / 256), dim3(256), st, p, n);
 }
 
 hipError_t launch_u64_zero(hipStream_t st, unsigned long long *p, int n)
 {
-    hipLaunchKernelGGL(u64_zero_kernel, dim3((n + 63) / 64), dim3(64), 0, st, p, n);
-    return hipGetLastError();
+    return launch_kernel(u64_zero_kernel, dim3((n + 63) / 64), dim3(64), st, p, n);
 }
 
 }  // namespace su3hb

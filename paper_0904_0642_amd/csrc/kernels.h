@@ -3,9 +3,20 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "layout.h"
 
 namespace su3hb {
+
+// A launch and its own status: hipGetLastError would also report, as this
+// launch's, an error that another call of the thread has left.
+template <typename... P>
+hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t st, std::common_type_t<P>... args)
+{
+    void *params[] = {&args...};
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, params, 0, st);
+}
 
 // checkerboard slice update (one colour, one direction, all replicas);
 // waves = minimum waves per SIMD the kernel was built for (2, or 3 for D = 4)

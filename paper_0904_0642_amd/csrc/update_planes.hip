@@ -270,10 +270,8 @@ static hipError_t launch_planes_t(hipStream_t st, const UpdateArgs &a)
 {
     const dim3 grid((a.total_blocks + 7) / 8 * 8), block(64 * D);
     if (a.meas != nullptr && a.parity == 1 && a.meas_classes == 3)
-        hipLaunchKernelGGL((update_planes_kernel<D, PREC, 3>), grid, block, 0, st, a);
-    else
-        hipLaunchKernelGGL((update_planes_kernel<D, PREC, 1>), grid, block, 0, st, a);
-    return hipGetLastError();
+        return launch_kernel(update_planes_kernel<D, PREC, 3>, grid, block, st, a);
+    return launch_kernel(update_planes_kernel<D, PREC, 1>, grid, block, st, a);
 }
 
 template <int D>

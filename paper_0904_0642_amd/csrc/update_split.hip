@@ -259,10 +259,8 @@ static hipError_t launch_small_t(hipStream_t st, const SmallArgs &s)
     // a block for every group on whichever XCD begins first (small_team)
     const dim3 grid(8u * s.u.total_blocks), block(256);
     if (s.u.meas != nullptr && s.u.meas_classes == 3)
-        hipLaunchKernelGGL((update_small_kernel<D, PREC, 3>), grid, block, 0, st, s);
-    else
-        hipLaunchKernelGGL((update_small_kernel<D, PREC, 1>), grid, block, 0, st, s);
-    return hipGetLastError();
+        return launch_kernel(update_small_kernel<D, PREC, 3>, grid, block, st, s);
+    return launch_kernel(update_small_kernel<D, PREC, 1>, grid, block, st, s);
 }
 
 template <int D>
@@ -282,10 +280,8 @@ static hipError_t launch_split_t(hipStream_t st, const UpdateArgs &a)
 {
     const dim3 grid((a.total_blocks + 7) / 8 * 8), block(256);
     if (a.meas != nullptr && a.parity == 1 && a.meas_classes == 3)
-        hipLaunchKernelGGL((update_split_kernel<D, PREC, 3>), grid, block, 0, st, a);
-    else
-        hipLaunchKernelGGL((update_split_kernel<D, PREC, 1>), grid, block, 0, st, a);
-    return hipGetLastError();
+        return launch_kernel(update_split_kernel<D, PREC, 3>, grid, block, st, a);
+    return launch_kernel(update_split_kernel<D, PREC, 1>, grid, block, st, a);
 }
 
 template <int D>
