@@ -5,11 +5,13 @@
 // that hold whole sweeps.  Usage: capi_host <scenario>; prints what went wrong
 // and exits with 1, or nothing and 0.
 #include <hip/hip_runtime.h>
+#include <unistd.h>
 
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <filesystem>
 #include <map>
 #include <string>
 #include <vector>
@@ -27,6 +29,9 @@ int g_fail_in = -1;                  // launches until one fails; -1: none
 uint32_t g_swept = 0;                // last sweep index that a slice drew with
 uint32_t g_slices = 0;               // slices done
 bool g_give_up = false;              // launches of whole sweeps give up a wait
+bool g_busy = false;                 // work that was there before runs on the stream
+int g_polls = 0;                     // event queries meanwhile
+size_t g_differ = 0;                 // doubles that a copy of links got wrong
 
 void bad(const char *fmt, ...)
 {
@@ -51,6 +56,13 @@ bool in_memory(const void *p, size_t bytes)
         if (static_cast<const char *>(p) >= m.first && static_cast<const char *>(p) + bytes <= m.first + m.second)
             return true;
     return false;
+}
+
+int threads()
+{
+    int n = 0;
+    for (const auto &f : std::filesystem::directory_iterator("/proc/self/task")) n += f.exists();
+    return n;
 }
 
 // what a slice kernel does besides its links
@@ -111,13 +123,26 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *)
     return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t)
+{
+    if (g_busy && threads() != 1) bad("%d threads while the stream is waited for", threads());
+    g_busy = false;
+    return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) { *e = reinterpret_cast<hipEvent_t>(1); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t)
+{
+    if (!g_busy) return hipSuccess;
+    usleep(100);
+    if (++g_polls < 100) return hipErrorNotReady;
+    bad("%d threads poll while earlier work runs", threads());
+    g_busy = false;
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
 
@@ -175,8 +200,19 @@ hipError_t launch_measure_finalize(hipStream_t, const double *meas, int n, int D
     return hipSuccess;
 }
 hipError_t launch_start(int, int, hipStream_t, void *, const RepDesc *, int, uint32_t, int) { return launch(); }
-hipError_t launch_pack(int, int, hipStream_t, const void *, const RepDesc *, int, uint64_t, uint32_t, double *) { return launch(); }
-hipError_t launch_unpack(int, int, hipStream_t, void *, const RepDesc *, int, uint64_t, uint32_t, const double *) { return launch(); }
+// element i of the canonical links is i
+hipError_t launch_pack(int D, int, hipStream_t, const void *, const RepDesc *, int, uint64_t c0, uint32_t count, double *dst)
+{
+    if (hipError_t e = launch()) return e;
+    for (size_t i = 0, n = size_t(D) * 18; i < count * n; ++i) dst[i] = double(c0 * n + i);
+    return hipSuccess;
+}
+hipError_t launch_unpack(int D, int, hipStream_t, void *, const RepDesc *, int, uint64_t c0, uint32_t count, const double *src)
+{
+    if (hipError_t e = launch()) return e;
+    for (size_t i = 0, n = size_t(D) * 18; i < count * n; ++i) g_differ += src[i] != double(c0 * n + i);
+    return hipSuccess;
+}
 hipError_t launch_validate(hipStream_t, const double *, uint64_t, unsigned long long *) { return launch(); }
 hipError_t launch_rep_set(hipStream_t, const RepDesc &r, RepDesc *d) { *d = r; return launch(); }
 hipError_t launch_stats_zero(hipStream_t, StatSlot *) { return launch(); }
@@ -373,6 +409,31 @@ void failed_clearing()
         }
 }
 
+// Large copies of links behind sweeps that still run: no thread is started before
+// the sweeps have ended.
+void copies_behind_sweeps()
+{
+    for (const std::vector<int> &ext : {std::vector<int>{8, 8, 8, 16}, {16, 16, 16, 16}, {16, 16, 30, 66}}) {
+        su3hb_lattice *L = lattice(ext);
+        size_t n = 4 * 18;
+        for (int e : ext) n *= size_t(e);
+        std::vector<double> links(n, -1.0);
+        EXPECT(su3hb_sweep(L, 6, 6, 8, 1, nullptr) == SU3HB_OK);
+        g_busy = true;
+        g_polls = 0;
+        EXPECT(su3hb_get_links(L, links.data(), n) == SU3HB_OK);
+        size_t differ = 0;
+        for (size_t i = 0; i < n; ++i) differ += links[i] != double(i);
+        EXPECT(differ == 0 && !g_busy);
+        g_busy = true;
+        g_polls = 0;
+        g_differ = 0;
+        EXPECT(su3hb_set_links(L, links.data(), n) == SU3HB_OK);
+        EXPECT(g_differ == 0 && !g_busy);
+        su3hb_free(L);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -382,6 +443,7 @@ int main(int argc, char **argv)
         {"failed_sweeps", failed_sweeps},
         {"given_up_waits", given_up_waits},
         {"failed_clearing", failed_clearing},
+        {"copies_behind_sweeps", copies_behind_sweeps},
     };
     const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
     if (it == scenarios.end()) return 2;

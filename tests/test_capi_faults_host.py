@@ -28,7 +28,8 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["failed_measurement", "failed_sweeps", "given_up_waits", "failed_clearing"])
+@pytest.mark.parametrize("scenario", ["failed_measurement", "failed_sweeps", "given_up_waits", "failed_clearing",
+                                      "copies_behind_sweeps"])
 def test_scenario(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[:4000] + r.stderr
