@@ -177,11 +177,12 @@ def overrelax_leg(name: str, steps: int, warmup: int, autotune_ms: int):
 
 
 def batch_leg(steps: int, warmup: int, n_hit: int, autotune_ms: int, nrep: int = 128, launch=None,
-              modes=("graph_per_slice", "persistent")):
+              modes=("per_slice", "persistent")):
     """Independent replicas of mixed sizes (8^4, 12^4, 16^3x4 round robin),
     beta uniform in [5.5, 6.5], FP32 links, one launch per slice for all
-    replicas (the label keeps its old name), and the same sweeps as one
-    persistent cooperative launch."""
+    replicas, and the same sweeps as one persistent cooperative launch, each
+    after warmup sweeps of its own (a process's first cooperative launch costs
+    about 5 ms)."""
     import torch
 
     import paper_0904_0642_amd as su3hb
@@ -198,11 +199,13 @@ def batch_leg(steps: int, warmup: int, n_hit: int, autotune_ms: int, nrep: int =
     shape = su3hb.su3hb_get_launch(b._h)
     if warmup > 0:
         b.sweep(n_hit=n_hit, n_sweeps=warmup, mode=0)
+        if "persistent" in modes:
+            b.sweep(n_hit=n_hit, n_sweeps=warmup, mode=1)
     links = t.links_per_sweep
     timing, _ = su3hb.su3hb_sweep_timed(b._h, 0.0, 0.0, n_hit, steps, measure=False)
     upd_ms = timing[0] / max(timing[1], 1)
     out = {}
-    for mode, label in ((0, "graph_per_slice"), (1, "persistent")):
+    for mode, label in ((0, "per_slice"), (1, "persistent")):
         if label not in modes:
             continue
         torch.cuda.synchronize()
@@ -447,8 +450,8 @@ def main():
     ap.add_argument("--extra-legs", default=",".join(EXTRA_LEGS),
                     help="comma-separated subset of the extra legs to run: " + ", ".join(EXTRA_LEGS))
     ap.add_argument("--batch-launch", default="", help="block,order,waves for the batch leg instead of autotuning")
-    ap.add_argument("--batch-modes", default="graph_per_slice,persistent",
-                    help="batch modes to time: graph_per_slice, persistent (cooperative launch)")
+    ap.add_argument("--batch-modes", default="per_slice,persistent",
+                    help="batch modes to time: per_slice, persistent (cooperative launch)")
     ap.add_argument("--copy-calibration-mib", type=int, default=0,
                     help="first run a plain device-to-device copy of this many MiB (for scaling HBM counters)")
     args = ap.parse_args()
