@@ -207,11 +207,12 @@ int su3hb_set_state(su3hb_lattice *lat, uint64_t seed, uint64_t sweep);
  * every shape.  get_launch reports the order in effect (with the 8 and 16).
  * Until a shape is set (here or by su3hb_autotune), lattices and batches whose
  * slices hold few links (from 20480 to 49152 by dimension and precision) share
- * every link's update between lanes or waves, and calls on those of at most 1024 links per slice run all their
- * sweeps in one launch (in blocks of one XCD that wait for each other's
- * slices; a wait past its limit ends the launch, and the calls that synchronise,
- * but set_state, return SU3HB_EHIP until set_links has replaced the links, of a
- * batch those of every replica).  The shape then stands for nothing.
+ * every link's update between lanes or waves, and calls on those of at most
+ * 1024 links per slice run all their sweeps in one launch (in blocks of one XCD
+ * that wait for each other's slices; a wait past its limit ends the launch, and
+ * the calls that synchronise, but set_state, return SU3HB_EHIP until set_links
+ * has replaced the links, of a batch those of every replica).  The shape then
+ * stands for nothing.
  * A shape whose LDS (staple snapshots of a measured slice plus staging
  * areas) exceeds the device's per-block limit returns SU3HB_EUNSUPPORTED
  * and leaves the launch shape as it was. */
@@ -294,13 +295,15 @@ void su3hb_batch_free(su3hb_batch *b);
  * no copy, no synchronisation) and returns before the GPU finishes, so it can
  * be captured into a graph.
  *
- * The kernels' counters, statistics and partial sums live in one static
- * device array of 8 MiB per GPU, held until the process ends and shared by
- * every call on that GPU: calls that overlap on one GPU (two streams, two
+ * The lattice's descriptor, the sweep counter and the partial sums live in one
+ * static device array of 8 MiB per GPU, held until the process ends and shared
+ * by every call on that GPU: calls that overlap on one GPU (two streams, two
  * threads) race.  Each call clears what must start at zero.  With series
- * non-NULL the measurement needs D * ceil(nlat * V / 512) * (1 or 3)
- * partial sums (3 for two layers) in that array, at most (8 MiB - 33 KiB) / 8;
- * a larger lattice returns SU3HB_EINVAL (64^4 fits; 128^4 does not).  Other
+ * non-NULL the measurement needs D * blocks * (1 or 3) partial sums (3 for two
+ * layers) in that array, at most (8 MiB - 33 KiB) / 8, a block being 256 links
+ * of a slice, or 16 or 64 where those are shared between lanes or waves (see
+ * su3hb_set_launch; these always fit); a larger lattice returns SU3HB_EINVAL
+ * (64^4 fits; 128^4 does not).  Other
  * errors as su3hb_init_lattice and su3hb_sweep, all reported before any
  * device work; the links are left unchanged then. */
 int su3hb_sweep_measure_static(const su3hb_params *p, double beta0, double beta1, int n_hit, int n_sweeps,

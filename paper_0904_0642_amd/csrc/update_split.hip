@@ -135,6 +135,12 @@ __device__ __forceinline__ void small_finish(const SmallArgs &s, uint32_t wave, 
 // FP64-18, 128 links), 14.7 and 5.9 us for 8^3x4 (1024 links); sums of one word
 // by all blocks instead of a word per group, or words written past the L2, made
 // the latter 9 to 13 us.
+//
+// FP64 kernels spill registers from D = 5 on (8 at D = 5, 23 to 25 at D = 6) and
+// where two layers are measured (18 to 28 at D = 4, up to 146 at D = 6).  They stay the
+// faster form: a slice of D = 6 takes 5.5 to 7.0 us for 32 to 1024 links (13.6 to 17.2
+// one thread per link, 7.6 shared by itself at 1536 links), measured on two layers
+// 9.0 to 13.8 (16.5 to 21.8).
 template <int D, int PREC, int NC>
 __global__ void __launch_bounds__(256, 2) update_small_kernel(SmallArgs s)
 {
