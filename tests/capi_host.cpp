@@ -308,6 +308,29 @@ void failed_sweeps()
             su3hb_free(L);
             if (!failed) break;
         }
+    // a batch, slice by slice and in persistent launches
+    su3hb_replica_desc reps[2] = {};
+    for (auto &r : reps) {
+        for (int i = 0; i < 4; ++i) r.extents[i] = 8;
+        r.beta = 6;
+        r.start = SU3HB_COLD;
+    }
+    for (int mode = 0; mode < 2; ++mode)
+        for (int k = 0;; ++k) {
+            su3hb_batch *B = nullptr;
+            EXPECT(su3hb_batch_create(&B, 4, reps, 2, SU3HB_FP64_18, nullptr) == SU3HB_OK);
+            EXPECT(su3hb_batch_sweep(B, 8, 2, 0, nullptr) == SU3HB_OK);
+            g_fail_in = k;
+            const int rc = su3hb_batch_sweep(B, 8, 3, mode, nullptr);
+            const bool failed = g_fail_in < 0;
+            g_fail_in = -1;
+            EXPECT(rc == (failed ? SU3HB_EHIP : SU3HB_OK));
+            const uint64_t at = sweep_of(B);
+            EXPECT(su3hb_batch_sweep(B, 8, 1, 1 - mode, nullptr) == SU3HB_OK);
+            EXPECT(g_swept == at);
+            su3hb_batch_free(B);
+            if (!failed) break;
+        }
 }
 
 // A launch of whole sweeps gives up a wait.  Every call that synchronises says so,
