@@ -785,16 +785,23 @@ bool have_ring(su3hb_lattice *L)
     return ok;
 }
 
+// Before a copy through the ring.  A captured stream is left as it is: waiting
+// would end the capture, and its events would never end.
+int idle_stream(su3hb_lattice *L)
+{
+    if (int rc = refuse_capture(L)) return rc;
+    HIPCHK(hipStreamSynchronize(L->stream));
+    return SU3HB_OK;
+}
+
 // This thread makes all calls of the runtime, the threads it starts copy parts
 // of pieces.  Piece c uses slot c % kRingSlots; the threads have it while
 // open > c and not all its parts are copied, else the copy engine has it.
 // Returns with the copy complete, or kNoRing with nothing done.  All threads poll:
-// the caller waits for what the stream held before, sweeps perhaps, ahead of it.
+// the caller waits for what the stream held before, sweeps perhaps (idle_stream).
 constexpr int kNoRing = 1;
 int ring_copy(su3hb_lattice *L, char *host, char *dev, size_t bytes, bool to_device)
 {
-    // events of a captured stream never end
-    if (int rc = refuse_capture(L)) return rc;
     if (!have_ring(L)) return kNoRing;
     const uint32_t n = uint32_t((bytes + kRingSlot - 1) / kRingSlot);
     char *ring = static_cast<char *>(L->ring);
@@ -862,7 +869,7 @@ int ring_copy(su3hb_lattice *L, char *host, char *dev, size_t bytes, bool to_dev
 int upload_stage(su3hb_lattice *L, const double *host, size_t bytes)
 {
     if (bytes >= kRingMinUp && is_pageable(host)) {
-        HIPCHK(hipStreamSynchronize(L->stream));
+        if (int rc = idle_stream(L)) return rc;
         const int rc = ring_copy(L, const_cast<char *>(reinterpret_cast<const char *>(host)),
                                  reinterpret_cast<char *>(L->d_stage), bytes, true);
         if (rc != kNoRing) return rc;
@@ -900,7 +907,8 @@ int get_replica_links(su3hb_lattice *L, int r, double *host, size_t n)
         const bool by_ring = bytes >= kRingMinDown && is_pageable(host + c0 * per_site);
         // (before the conversion, which the start of the threads hides: 4.7 MB 201 us,
         // after it 211)
-        if (by_ring) HIPCHK(hipStreamSynchronize(L->stream));
+        if (by_ring)
+            if (int rc = idle_stream(L)) return rc;
         HIPCHK(launch_pack(L->nd, L->prec, L->stream, L->links, L->d_reps, r, c0, cnt, L->d_stage));
         if (int rc = download_stage(L, host + c0 * per_site, bytes, by_ring)) return rc;
     }

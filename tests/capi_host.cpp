@@ -29,6 +29,7 @@ int g_fail_in = -1;                  // launches until one fails; -1: none
 uint32_t g_swept = 0;                // last sweep index that a slice drew with
 uint32_t g_slices = 0;               // slices done
 bool g_give_up = false;              // launches of whole sweeps give up a wait
+bool g_capturing = false;            // the stream is being captured
 bool g_busy = false;                 // work that was there before runs on the stream
 int g_polls = 0;                     // event queries meanwhile
 size_t g_differ = 0;                 // doubles that a copy of links got wrong
@@ -122,9 +123,14 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *)
     at->type = hipMemoryTypeUnregistered;
     return hipSuccess;
 }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
+{
+    *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipStreamSynchronize(hipStream_t)
 {
+    if (g_capturing) bad("a captured stream is waited for");
     if (g_busy && threads() != 1) bad("%d threads while the stream is waited for", threads());
     g_busy = false;
     return hipSuccess;
@@ -239,7 +245,7 @@ hipError_t launch_u64_zero(hipStream_t, unsigned long long *p, int n)
 
 namespace {
 
-su3hb_lattice *lattice(std::vector<int> ext)
+su3hb_lattice *lattice(std::vector<int> ext, void *stream = nullptr)
 {
     su3hb_params p{};
     p.nd = int(ext.size());
@@ -247,6 +253,7 @@ su3hb_lattice *lattice(std::vector<int> ext)
     p.nlat = 1;
     p.start = SU3HB_COLD;
     p.seed = 1;
+    p.hip_stream = stream;
     su3hb_lattice *L = nullptr;
     if (su3hb_init_lattice(&L, &p) != SU3HB_OK) {
         bad("no lattice: %s", su3hb_last_error());
@@ -437,7 +444,8 @@ void failed_clearing()
 void copies_behind_sweeps()
 {
     for (const std::vector<int> &ext : {std::vector<int>{8, 8, 8, 16}, {16, 16, 16, 16}, {16, 16, 30, 66}}) {
-        su3hb_lattice *L = lattice(ext);
+        static int stream;  // not the null stream, which cannot be captured
+        su3hb_lattice *L = lattice(ext, &stream);
         size_t n = 4 * 18;
         for (int e : ext) n *= size_t(e);
         std::vector<double> links(n, -1.0);
@@ -453,6 +461,11 @@ void copies_behind_sweeps()
         g_differ = 0;
         EXPECT(su3hb_set_links(L, links.data(), n) == SU3HB_OK);
         EXPECT(g_differ == 0 && !g_busy);
+        // a captured stream is refused without a wait, which would end the capture
+        g_capturing = true;
+        EXPECT(su3hb_get_links(L, links.data(), n) == SU3HB_EHIP);
+        if (n * sizeof(double) >= size_t(32) << 20) EXPECT(su3hb_set_links(L, links.data(), n) == SU3HB_EHIP);
+        g_capturing = false;
         su3hb_free(L);
     }
 }
